@@ -364,7 +364,7 @@ int adapld_ngram_index_build(const int32_t* tokens, const int32_t* lens, int B, 
                              void* index, size_t index_bytes, hipStream_t stream) {
   if (const int st = check_ngram(tokens, lens, index, index_bytes, B, L_stride, n_max); st != ADAPLD_OK || B == 0)
     return st;
-  return hip_status(adapld::launch_ngram_update(tokens, lens, B, L_stride, n_max, index, 1, stream));
+  return hip_status(adapld::launch_ngram_build(tokens, lens, B, L_stride, n_max, index, stream));
 }
 
 int adapld_ngram_index_append(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max,

@@ -142,10 +142,9 @@ hipError_t launch_successor_embed(const int32_t* tokens, const int32_t* lens, co
                                   const int32_t* branch_tok, uint8_t* flags, int32_t* lists,
                                   int32_t* counts, hipStream_t stream);
 
-// Builds (rebuild = 1) or brings up to date (0) the n-gram index of every
-// sequence; then answers the lexical match from it.
-hipError_t launch_ngram_update(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max,
-                               void* index, int rebuild, hipStream_t stream);
+// Builds the n-gram index of every sequence from scratch.
+hipError_t launch_ngram_build(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max,
+                              void* index, hipStream_t stream);
 // Brings the index up to date after appends; with cand_pos also answers the
 // lexical match in the same launch.
 hipError_t launch_ngram_append(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max, void* index,

@@ -12,15 +12,18 @@
 // array moves to one of twice the capacity (the pool never needs more than
 // 12 ints per context token; see ngram_pool_ints).
 //
-// update kernel: one workgroup per (level, sequence).  The positions that
-// became candidates since the last update (all of them for a build, or
-// when the context shrank) are inserted in batches of 256 in ascending
-// order: each batch is sorted by 64-bit n-gram hash, equal n-grams form
-// contiguous groups (checked token by token; a hash collision inside a batch
-// falls back to inserting that batch one position at a time), each group's
-// first thread finds or creates its slot and reserves room, arrays that
-// overflow are copied by the whole workgroup, and every thread writes its
-// position at its rank inside its group, so every array stays ascending.
+// build kernel: one workgroup per region of a level's table (see its comment).
+//
+// update kernel (appends with more levels than one workgroup has waves): one
+// workgroup per (level, sequence).  The positions that became candidates since
+// the last update (all of them when the context shrank) are inserted in
+// batches of 256 in ascending order: each batch is sorted by n-gram hash,
+// equal n-grams form contiguous groups (checked token by token; a hash
+// collision inside a batch falls back to inserting that batch one position at
+// a time), each group's first thread finds or creates its slot and reserves
+// room, arrays that overflow are copied by the whole workgroup, and every
+// thread writes its position at its rank inside its group, so every array
+// stays ascending.
 //
 // append kernel: one workgroup per sequence, one wave per level, each wave
 // inserting its level's new positions 64 at a time (a register bitonic sort
@@ -34,6 +37,8 @@
 // match kernel: one workgroup per sequence; lane n-1 of the first wave looks
 // up the last n tokens at level n, the longest level with a hit gives n*,
 // and its array is copied out as C_lex: one contiguous read.
+#include <algorithm>
+
 #include "adapld_internal.h"
 #include "device_utils.h"
 
@@ -57,6 +62,7 @@ struct NgHeader {
 };
 
 constexpr int kNgMagic = 0x6e677231;
+constexpr size_t kNgRegion = 8192;   // slots per region (a smaller table is one region)
 
 struct NgLevel {
   NgSlot* tab;
@@ -79,35 +85,61 @@ __device__ __forceinline__ NgLevel ng_level(void* index, int b, int n, int n_max
   return l;
 }
 
-// 64-bit hash of the n tokens ending at j, newest first.
+// Hash of the n tokens ending at j, newest first: two multiplicative 32-bit
+// chains (the low one places the n-gram in the table; a 64-bit product costs
+// several quarter-rate multiplies), each finished by murmur3's avalanche step.
+// The tokens are loaded four at a time, so that they share a memory round
+// trip (the loads past the n-gram repeat its oldest token).
+__device__ __forceinline__ uint32_t ng_mix(uint32_t h, uint32_t t) {
+  h = (h ^ t) * 0x9E3779B1u;
+  return h ^ (h >> 15);
+}
+__device__ __forceinline__ uint32_t ng_finish(uint32_t h) {
+  h = (h ^ (h >> 16)) * 0x85EBCA6Bu;
+  h = (h ^ (h >> 13)) * 0xC2B2AE35u;
+  return h ^ (h >> 16);
+}
 __device__ __forceinline__ uint64_t ng_hash(const int32_t* M, int j, int n) {
-  uint64_t h = 0x243F6A8885A308D3ull ^ (uint64_t)n;
-  for (int i = 0; i < n; ++i) {
-    h ^= (uint32_t)M[j - i];
-    h *= 0x100000001B3ull;
-    h ^= h >> 29;
+  uint32_t lo = (uint32_t)n, hi = ~(uint32_t)n;
+  for (int i0 = 0; i0 < n; i0 += 4) {
+    int t[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = M[j - min(i0 + i, n - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i0 + i < n) {
+        lo = ng_mix(lo, (uint32_t)t[i]);
+        hi = ng_mix(hi, (uint32_t)t[i] * 0x85EBCA77u);
+      }
+    }
   }
-  h ^= h >> 30;
-  h *= 0xBF58476D1CE4E5B9ull;
-  h ^= h >> 27;
-  h *= 0x94D049BB133111EBull;
-  h ^= h >> 31;
-  return h;
+  return ((uint64_t)ng_finish(hi) << 32) | ng_finish(lo);
 }
 
 __device__ __forceinline__ bool ng_equal(const int32_t* M, int j0, int j1, int n) {
-  for (int i = 0; i < n; ++i)
-    if (M[j0 - i] != M[j1 - i]) return false;
+  for (int i0 = 0; i0 < n; i0 += 4) {
+    int x[4], y[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = min(i0 + i, n - 1);
+      x[i] = M[j0 - k];
+      y[i] = M[j1 - k];
+    }
+    if (x[0] != y[0] || x[1] != y[1] || x[2] != y[2] || x[3] != y[3]) return false;
+  }
   return true;
 }
 
 // The slot of the n-gram ending at j (creating it when `insert`), or -1 when
-// it is absent.  The table is at most half full, so an empty slot ends every
-// probe; the loop is bounded by the table size all the same.
+// it is absent.  Probing is linear and wraps inside the slot's region of
+// kNgRegion slots, so that a build can give each region to one workgroup.
+// The table is at most half full, so an empty slot ends every probe; the loop
+// is bounded by the region's size all the same.
 __device__ int ng_probe(const NgLevel& lv, const int32_t* M, int j, int n, uint64_t h, bool insert, bool& created) {
   created = false;
   size_t s = h & lv.mask;
-  for (size_t step = 0; step <= lv.mask; ++step, s = (s + 1) & lv.mask) {
+  const size_t rm = lv.mask < kNgRegion - 1 ? lv.mask : kNgRegion - 1;
+  for (size_t step = 0; step <= rm; ++step, s = (s & ~rm) | ((s + 1) & rm)) {
     int k = __hip_atomic_load(&lv.tab[s].key_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (k < 0) {
       if (!insert) return -1;
@@ -367,7 +399,6 @@ struct NgArgs {
   const int32_t* lens;
   void* index;
   int B, L_stride, n_max;
-  int rebuild;
 };
 
 __global__ __launch_bounds__(kNgThreads) void ngram_update_kernel(const NgArgs a) {
@@ -379,8 +410,8 @@ __global__ __launch_bounds__(kNgThreads) void ngram_update_kernel(const NgArgs a
   const int L = min(max(a.lens[b], 0), a.L_stride);
   if (threadIdx.x == 0) {
     const NgHeader h = *lv.hdr;
-    // A build, a context that shrank or an unusable level starts from scratch.
-    const bool fresh = a.rebuild || h.magic != kNgMagic || L < h.indexed_len || h.indexed_len < 0 || h.overflow;
+    // A level never built, a context that shrank or an unusable level starts from scratch.
+    const bool fresh = h.magic != kNgMagic || L < h.indexed_len || h.indexed_len < 0 || h.overflow;
     s_top = fresh ? 0 : h.pool_top;
     s_over = 0;
     s_start = fresh ? -1 : max(n - 1, h.indexed_len - 1);
@@ -395,6 +426,276 @@ __global__ __launch_bounds__(kNgThreads) void ngram_update_kernel(const NgArgs a
   // candidate end positions [j0, L-2], in batches, ascending
   for (int lo = j0; lo <= L - 2; lo += kNgThreads) ng_insert_batch(lv, M, n, lo, min(kNgThreads, L - 1 - lo), &s_top, &s_over);
   if (threadIdx.x == 0) *lv.hdr = NgHeader{s_top, L, s_over, kNgMagic};
+}
+
+// ------------------------------------------------------------------ build
+// From scratch, a level is built by one workgroup per region of its table:
+// the workgroup lists the positions whose n-gram falls into its region, in
+// ascending order, groups them in a copy of the region's keys in LDS, sizes
+// every group's array with one reservation of the pool, and writes the whole
+// region, empty slots included, in one coalesced pass (so nothing has to be
+// cleared first and no global atomic is taken per n-gram).  A position's rank
+// in its array is the number of smaller list indices in its group: counted in
+// LDS for a small group, by a bitmap of the list for a large one.  More
+// positions than one list holds are counted list by list first, then listed
+// again and placed.
+//
+// What bounds it: the latency of a dozen dependent phases and the writing of
+// the table (16 bytes per slot, at least two slots per position of capacity).
+// Build calls with 4 levels, against one workgroup per level that sorted 256
+// positions at a time: 16 x 8192 tokens 31.9 us (417; 56 for workgroups that
+// claimed slots of a cleared table by global atomics), 8 x 32768 193 (1672),
+// 1 x 131072 337 (6488), 64 x 2048 23.5 (115), 1 x 512 12.3 (25.7).  Every
+// region's workgroup hashes the whole row, which is what the longer rows pay.
+constexpr int kBuildThreads = 1024;
+constexpr int kBuildWaves = kBuildThreads / kWave;
+constexpr int kBuildItems = 4096;            // listed positions
+constexpr int kBuildRun = 8;                 // positions per thread and round
+constexpr int kBuildSlots = (int)kNgRegion / kBuildThreads;   // table slots per thread
+constexpr int kBuildSmall = 32;              // largest group ranked by counting
+
+// Exclusive prefix of v over the workgroup in thread order; *sum gets the sum.
+__device__ __forceinline__ int build_scan(int v, int* s_red, int* sum) {
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int incl = wave_incl_scan_i32(v);
+  __syncthreads();   // earlier reads of s_red are done
+  if (lane == kWave - 1) s_red[wave] = incl;
+  __syncthreads();
+  const int sums = wave_incl_scan_i32(lane < kBuildWaves ? s_red[lane & (kBuildWaves - 1)] : 0);
+  *sum = __builtin_amdgcn_readlane(sums, kWave - 1);
+  return incl - v + (wave > 0 ? __builtin_amdgcn_readlane(sums, wave - 1) : 0);
+}
+
+struct BuildShared {
+  int key[kNgRegion];            // an end position of the slot's n-gram, -1: empty
+  int cnt[kNgRegion];            // its positions; then the pool index of the next one to place (-1: no room)
+  uint16_t num[kNgRegion];       // its positions in the current list
+  uint16_t first[kNgRegion];     // its first place in grp, then one past its last
+  int pos[kBuildItems];          // the list, ascending
+  uint16_t slot[kBuildItems];    // its slots
+  uint16_t grp[kBuildItems];     // list indices, group by group
+  uint16_t big[kBuildItems / kBuildSmall];
+  uint32_t map[kBuildWaves][kBuildItems / 32];
+  int red[kBuildWaves];
+  int base, nbig, over;
+};
+
+// Finds (or claims) the slots of the listed positions s.pos[0, count).
+__device__ __forceinline__ void build_group(const int32_t* __restrict__ M, int n, int rm, int count, BuildShared& s) {
+  for (int i = threadIdx.x; i < count; i += kBuildThreads) {
+    const int j = s.pos[i];
+    int at = (int)(uint32_t)ng_hash(M, j, n) & rm;
+    int step = 0;
+    for (; step <= rm; ++step, at = (at + 1) & rm) {
+      const int o = atomicCAS(&s.key[at], -1, j);
+      if (o == -1 || ng_equal(M, o, j, n)) break;
+    }
+    if (step > rm) s.over = 1;   // a full region: the level is marked unusable
+    s.slot[i] = (uint16_t)at;
+  }
+}
+
+// Writes the listed positions to their groups' arrays, ascending.
+__device__ __forceinline__ void build_place(const NgLevel& lv, int nslots, int count, BuildShared& s) {
+  const int tid = threadIdx.x;
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  for (int i = tid; i < nslots / 2; i += kBuildThreads) reinterpret_cast<uint32_t*>(s.num)[i] = 0u;
+  if (tid == 0) s.nbig = 0;
+  __syncthreads();
+  // 16-bit counters two to a word: a list has at most kBuildItems of either
+  for (int i = tid; i < count; i += kBuildThreads) {
+    const int sl = s.slot[i];
+    atomicAdd(reinterpret_cast<uint32_t*>(s.num) + (sl >> 1), 1u << (16 * (sl & 1)));
+  }
+  __syncthreads();
+  int c[kBuildSlots], sum = 0, total;
+#pragma unroll
+  for (int q = 0; q < kBuildSlots; ++q) {
+    const int sl = tid + q * kBuildThreads;
+    c[q] = sl < nslots ? s.num[sl] : 0;
+    sum += c[q];
+  }
+  int at = build_scan(sum, s.red, &total);
+#pragma unroll
+  for (int q = 0; q < kBuildSlots; ++q) {
+    const int sl = tid + q * kBuildThreads;
+    if (c[q]) s.first[sl] = (uint16_t)at;
+    if (c[q] > kBuildSmall) s.big[atomicAdd(&s.nbig, 1)] = (uint16_t)sl;
+    at += c[q];
+  }
+  __syncthreads();
+  // list indices group by group, in any order inside a group
+  for (int i = tid; i < count; i += kBuildThreads) {
+    const int sl = s.slot[i];
+    const uint32_t old = atomicAdd(reinterpret_cast<uint32_t*>(s.first) + (sl >> 1), 1u << (16 * (sl & 1)));
+    s.grp[(old >> (16 * (sl & 1))) & 0xffffu] = (uint16_t)i;
+  }
+  __syncthreads();
+  for (int e = tid; e < count; e += kBuildThreads) {
+    const int i = s.grp[e];
+    const int sl = s.slot[i];
+    const int cr = s.num[sl];
+    const int dst = s.cnt[sl];
+    if (cr > kBuildSmall || dst < 0) continue;
+    const int g0 = s.first[sl] - cr;
+    int rank = 0;
+    for (int x = 0; x < cr; ++x) rank += s.grp[g0 + x] < i ? 1 : 0;
+    lv.pool[dst + rank] = s.pos[i];
+  }
+  for (int g = wave; g < s.nbig; g += kBuildWaves) {
+    const int sl = s.big[g];
+    const int cr = s.num[sl];
+    const int g0 = s.first[sl] - cr;
+    int dst = s.cnt[sl];
+    if (dst < 0) continue;
+    uint32_t* map = s.map[wave];
+    for (int w = lane; w < kBuildItems / 32; w += kWave) map[w] = 0u;
+    __threadfence_block();
+    for (int x = lane; x < cr; x += kWave) {
+      const int i = s.grp[g0 + x];
+      atomicOr(&map[i >> 5], 1u << (i & 31));
+    }
+    __threadfence_block();
+    for (int w0 = 0; w0 < kBuildItems / 32; w0 += kWave) {
+      uint32_t bits = map[w0 + lane];
+      const int incl = wave_incl_scan_i32(__popc(bits));
+      int to = dst + incl - __popc(bits);
+      dst += __builtin_amdgcn_readlane(incl, kWave - 1);
+      while (bits) {
+        const int e = __builtin_ctz(bits);
+        bits &= bits - 1;
+        lv.pool[to++] = s.pos[32 * (w0 + lane) + e];
+      }
+    }
+  }
+  __syncthreads();   // the list and the cursors are read
+  // the next list's positions follow this one's
+#pragma unroll
+  for (int q = 0; q < kBuildSlots; ++q) {
+    const int sl = tid + q * kBuildThreads;
+    if (c[q] && s.cnt[sl] >= 0) s.cnt[sl] += c[q];
+  }
+}
+
+__global__ __launch_bounds__(kBuildThreads) void ngram_build_kernel(const NgArgs a) {
+  __shared__ BuildShared s;
+  const int tid = threadIdx.x;
+  const int region = blockIdx.x;
+  const int n = blockIdx.y + 1;
+  const int b = blockIdx.z;
+  const NgLevel lv = ng_level(a.index, b, n, a.n_max, a.L_stride);
+  const int32_t* __restrict__ M = a.tokens + (size_t)b * a.L_stride;
+  const int L = min(max(a.lens[b], 0), a.L_stride);
+  const int nslots = (int)min(lv.mask + 1, kNgRegion);
+  const int rm = nslots - 1;
+  for (int i = tid; i < nslots; i += kBuildThreads) {
+    s.key[i] = -1;
+    s.cnt[i] = 0;
+  }
+  if (tid == 0) s.over = 0;
+
+  // Lists the region's positions among kBuildRun consecutive ones per thread
+  // and round, in order; use(count) gets every full list and the last one.
+  auto each_list = [&](auto use) {
+    int count = 0, lists = 0;
+    for (int j0 = n - 1; j0 <= L - 2; j0 += kBuildThreads * kBuildRun) {
+      const int j = j0 + tid * kBuildRun;
+      uint32_t h[kBuildRun];
+#pragma unroll
+      for (int e = 0; e < kBuildRun; ++e) h[e] = (uint32_t)n;
+      // token i of the hashes of the run: a window of tokens that moves back
+      int t[kBuildRun];
+#pragma unroll
+      for (int e = 0; e < kBuildRun; ++e) t[e] = M[min(j + e, L - 1)];
+      for (int i = 0; i < n; ++i) {
+        const int older = M[max(min(j, L - 1) - i - 1, 0)];
+#pragma unroll
+        for (int e = 0; e < kBuildRun; ++e) h[e] = ng_mix(h[e], (uint32_t)t[e]);
+#pragma unroll
+        for (int e = kBuildRun - 1; e > 0; --e) t[e] = t[e - 1];
+        t[0] = older;
+      }
+      uint32_t mine = 0;
+#pragma unroll
+      for (int e = 0; e < kBuildRun; ++e)
+        if (j + e <= L - 2 && (int)((ng_finish(h[e]) & lv.mask) / kNgRegion) == region) mine |= 1u << e;
+      int found;
+      int at = count + build_scan(__popc(mine), s.red, &found);
+      count += found;
+      const bool last = j0 + kBuildThreads * kBuildRun > L - 2;
+      for (;;) {
+        int k = at;
+        for (uint32_t m = mine; m; m &= m - 1, ++k)
+          if (k >= 0 && k < kBuildItems) s.pos[k] = j + __builtin_ctz(m);
+        if (count < kBuildItems && !last) break;
+        __syncthreads();   // the list (and, the first time, the empty region) is written
+        use(min(count, kBuildItems));
+        __syncthreads();   // ... and used
+        ++lists;
+        at -= kBuildItems;
+        count -= min(count, kBuildItems);
+        if (count == 0) break;
+      }
+    }
+    return lists;
+  };
+
+  int held = 0;   // size of the last list
+  const int lists = each_list([&](int count) {
+    build_group(M, n, rm, count, s);
+    __syncthreads();
+    for (int i = tid; i < count; i += kBuildThreads) atomicAdd(&s.cnt[s.slot[i]], 1);
+    held = count;
+  });
+  __syncthreads();
+  // One reservation for all arrays of the region, then its slots.
+  int need = 0, total;
+#pragma unroll
+  for (int q = 0; q < kBuildSlots; ++q) {
+    const int sl = tid + q * kBuildThreads;
+    if (sl < nslots && s.cnt[sl] > 0) need += pow2_at_least(s.cnt[sl]);
+  }
+  int off = build_scan(need, s.red, &total);
+  if (tid == 0) s.base = total > 0 ? atomicAdd(&lv.hdr->pool_top, total) : 0;
+  __syncthreads();
+  off += s.base;
+#pragma unroll
+  for (int q = 0; q < kBuildSlots; ++q) {
+    const int sl = tid + q * kBuildThreads;
+    if (sl < nslots) {
+      NgSlot v{-1, 0, 0, 0};
+      const int c = s.cnt[sl];
+      if (c > 0) {
+        const int cap = pow2_at_least(c);
+        const bool fits = off + cap <= lv.pool_ints;
+        if (!fits) s.over = 1;
+        v = NgSlot{s.key[sl], off, c, cap};
+        s.cnt[sl] = fits ? off : -1;
+        off += cap;
+      }
+      lv.tab[(size_t)region * kNgRegion + sl] = v;
+    }
+  }
+  __syncthreads();
+  if (tid == 0 && s.over) atomicOr(&lv.hdr->overflow, 1);
+  if (lists == 1) build_place(lv, nslots, held, s);
+  else if (lists > 1)
+    each_list([&](int count) {
+      build_group(M, n, rm, count, s);
+      __syncthreads();
+      build_place(lv, nslots, count, s);
+    });
+}
+
+// The headers of a build: nothing in use, the length it will reflect.
+__global__ void ngram_header_kernel(const NgArgs a) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= a.B * a.n_max) return;
+  const int b = i / a.n_max;
+  const NgLevel lv = ng_level(a.index, b, i - b * a.n_max + 1, a.n_max, a.L_stride);
+  *lv.hdr = NgHeader{0, min(max(a.lens[b], 0), a.L_stride), 0, kNgMagic};
 }
 
 // The lexical match of sequence b from its (up-to-date) index, by the first
@@ -501,16 +802,21 @@ __device__ void ng_match_seq(const NgArgs& a, int b, int32_t* __restrict__ cand_
 
 }  // namespace
 
-hipError_t launch_ngram_update(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max,
-                               void* index, int rebuild, hipStream_t stream) {
-  const NgArgs a{tokens, lens, index, B, L_stride, n_max, rebuild};
-  hipLaunchKernelGGL(ngram_update_kernel, dim3(n_max, B), dim3(kNgThreads), 0, stream, a);
+hipError_t launch_ngram_build(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max,
+                               void* index, hipStream_t stream) {
+  const NgArgs a{tokens, lens, index, B, L_stride, n_max};
+  hipLaunchKernelGGL(ngram_header_kernel, dim3((B * n_max + 255) / 256), dim3(256), 0, stream, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const size_t slots = ngram_slots(L_stride);
+  const unsigned regions = (unsigned)((slots + kNgRegion - 1) / kNgRegion);
+  hipLaunchKernelGGL(ngram_build_kernel, dim3(regions, n_max, B), dim3(kBuildThreads), 0, stream, a);
   return hipGetLastError();
 }
 
 hipError_t launch_ngram_append(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max, void* index,
                                int32_t* cand_pos, int32_t* cand_count, int32_t* match_n, hipStream_t stream) {
-  const NgArgs a{tokens, lens, index, B, L_stride, n_max, 0};
+  const NgArgs a{tokens, lens, index, B, L_stride, n_max};
   if (n_max > kNgAppendWaves) {   // more levels than one workgroup's waves: the build kernel's path
     hipLaunchKernelGGL(ngram_update_kernel, dim3(n_max, B), dim3(kNgThreads), 0, stream, a);
     hipError_t e = hipGetLastError();
@@ -529,7 +835,7 @@ hipError_t launch_ngram_append(const int32_t* tokens, const int32_t* lens, int B
 hipError_t launch_ngram_match(const int32_t* tokens, const int32_t* lens, const void* index, int B, int L_stride,
                               int n_max, int32_t* cand_pos, int32_t* cand_count, int32_t* match_n,
                               hipStream_t stream) {
-  const NgArgs a{tokens, lens, const_cast<void*>(index), B, L_stride, n_max, 0};
+  const NgArgs a{tokens, lens, const_cast<void*>(index), B, L_stride, n_max};
   hipLaunchKernelGGL(ngram_match_kernel, dim3(B), dim3(kNgThreads), 0, stream, a, cand_pos, cand_count, match_n);
   return hipGetLastError();
 }

@@ -146,3 +146,27 @@ def test_index_benchmark_workload():
         tok_d.copy_(torch.from_numpy(tok))
         lens_d.copy_(torch.from_numpy(lens))
         check(idx, tok, lens, tok_d, lens_d, cfg.n_max, f"step {step}", fused=True)
+
+
+@pytest.mark.parametrize("L,n_max", [(2, 1), (65, 4), (1025, 3), (2049, 4), (4100, 2), (9000, 5), (40000, 3), (70000, 2)])
+def test_index_build_sizes(L, n_max):
+    """Builds at the edges of the decomposition (positions per workgroup, parts,
+    several batches of one part's list): few distinct tokens (large groups),
+    many (small ones), one token throughout (every position in one part), and
+    shorter contexts in the same capacity; then one append on top."""
+    rng = np.random.default_rng(L + n_max)
+    cap = L + 70
+    tok = np.zeros((8, cap), np.int32)
+    for b, V in enumerate((3, 40, 1000, 100000, 1, 2, 300, 17)):
+        tok[b] = np.minimum(rng.integers(0, V, cap), rng.integers(0, V, cap)) - (b == 5)
+    s = rng.integers(0, L // 2 + 1)
+    tok[3, L - min(n_max, L // 2):L] = tok[3, s:s + min(n_max, L // 2)]   # a planted match
+    lens = np.array([L, L, L, L, L, L, L // 2, 1], np.int32)
+    tok_d, lens_d = torch.from_numpy(tok).cuda(), torch.from_numpy(lens).cuda()
+    idx = adapld.NgramIndex(8, cap, n_max)
+    for again in range(2):          # a second build over the first one's contents
+        idx.build(tok_d, lens_d)
+        check(idx, tok, lens, tok_d, lens_d, n_max, f"build {again}")
+    lens += rng.integers(0, 70, 8).astype(np.int32)
+    lens_d.copy_(torch.from_numpy(lens))
+    check(idx, tok, lens, tok_d, lens_d, n_max, "append", fused=True)
