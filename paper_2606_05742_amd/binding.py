@@ -114,10 +114,18 @@ def _check(status: int, what: str):
         raise AdapldError(status, f"{what}: {msg}")
 
 
+_Tensor = torch.Tensor
 _BF16_DTYPES = (torch.bfloat16, torch.int16, torch.uint16)
 
 
 def _ptr(t, name, dtypes, shape=None, nullable=False):
+    # A plain tensor that passes every check, in the fewest attribute reads:
+    # a call checks up to 19 tensors, which cost the host about 1 us each when
+    # every one went through the checks below (accept_greedy: 17.1 us per call,
+    # 10.9 with this; its kernel takes 5).
+    if (type(t) is _Tensor and t.is_cuda and t.dtype in dtypes and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return t.data_ptr()
     if t is None:
         if nullable:
             return None
@@ -135,10 +143,13 @@ def _ptr(t, name, dtypes, shape=None, nullable=False):
     return t.data_ptr()
 
 
+# The current device's current stream as an integer, without a Stream object.
+_current_device = torch.cuda.current_device
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    return _raw_stream(_current_device()) if stream is None else stream.cuda_stream
 
 
 def workspace_bytes(op, B, L_stride, d=0, k=0, T_max=0, Hq=0, Hkv=0, D=0) -> int:
