@@ -232,17 +232,19 @@ __device__ __forceinline__ uint64_t bitonic_sort_desc(uint64_t v) { return biton
 // the result of the full sort, in fewer steps (10 or 15 instead of 21).
 template <int N>
 __device__ __forceinline__ uint64_t bitonic_sort_desc_first(uint64_t v) { return bitonic_steps<2, 1, N>(v); }
-template <int K, int J>
+template <int K, int J, int KMAX = kWave>
 __device__ __forceinline__ uint32_t bitonic_steps_u32(uint32_t v) {
   const int lane = lane_id();
   const uint32_t p = xor_lanes_u32<J>(v);
   const bool keep_max = ((lane & J) == 0) == ((lane & K) == 0);
   v = keep_max ? (v > p ? v : p) : (v < p ? v : p);
-  if constexpr (J > 1) return bitonic_steps_u32<K, J / 2>(v);
-  else if constexpr (K < kWave) return bitonic_steps_u32<2 * K, K>(v);
+  if constexpr (J > 1) return bitonic_steps_u32<K, J / 2, KMAX>(v);
+  else if constexpr (K < KMAX) return bitonic_steps_u32<2 * K, K, KMAX>(v);
   else return v;
 }
 __device__ __forceinline__ uint32_t bitonic_sort_desc_u32(uint32_t v) { return bitonic_steps_u32<2, 1>(v); }
+template <int N>
+__device__ __forceinline__ uint32_t bitonic_sort_desc_first_u32(uint32_t v) { return bitonic_steps_u32<2, 1, N>(v); }
 
 // s_waitcnt vmcnt(n) (gfx9 encoding, n < 64); lgkmcnt and expcnt unconstrained.
 template <int N>

@@ -48,6 +48,7 @@
 // output's own) with the running max and sum in fp32; a combine kernel merges
 // them with log-sum-exp weights.
 #include <algorithm>
+#include <numeric>
 #include <type_traits>
 
 #include "adapld_internal.h"
@@ -86,12 +87,18 @@ struct VerifyArgs {
   const int32_t* lens;
   const int32_t* node_count;
   const uint64_t* tree_mask;
-  int L_stride, T_max, Hq, Hkv, G, rows_max, nsplit, chunk, nw, rowgroups, n_kvgroups;
+  int B, L_stride, T_max, Hq, Hkv, G, rows_max, nw;
+  int nsplit;      // splits per sequence in the plan (1: no sequence is split)
+  int chunk, rowgroups;   // context keys per split and row groups in the plan
+  int cap;         // most splits of one sequence (its slots in the workspace)
+  int max_wgs;     // workgroups that a split batch may take
+  int head_cols;   // XCDs that the heads of one (sequence, split) unit spread over: gcd(Hkv, 8)
   float scale_log2;
   uint16_t* out;
   float* lse;
-  uint16_t* ws_o;  // [B*Hkv][nsplit][rows_max][D]  partial outputs O/l, bf16
-  float2* ws_ml;   // [B*Hkv][nsplit][rows_max]     (running max in log2 units, sum)
+  uint16_t* ws_o;  // [B*Hkv][cap][rows_max][D]  partial outputs O/l, bf16
+  float2* ws_ml;   // [B*Hkv][cap][rows_max]     (running max in log2 units, sum)
+  int* ws_parts;   // [B]  splits of every sequence
 };
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
@@ -145,15 +152,16 @@ __device__ __forceinline__ void dma16_s_stream(const void* gbase, uint32_t voff,
 
 // The same share of a tile whose 64 keys are all below kend (no clamping):
 // the row addresses are a scalar base plus lane offsets fixed per wave.
-template <int WAVES, bool STREAM>
+template <int WAVES>
 __device__ __forceinline__ void issue_tile_full(const uint16_t* kb, const uint16_t* vb, int k0, uint32_t lk,
-                                                uint32_t lv, int wave, const uint32_t (&voff)[64 / WAVES / 4]) {
+                                                uint32_t lv, int wave, const uint32_t (&voff)[64 / WAVES / 4],
+                                                bool stream) {
   constexpr int kRowsPerWave = kKeyTile / WAVES;
 #pragma unroll
   for (int i = 0; i < kRowsPerWave / 4; ++i) {
     const int row0 = kRowsPerWave * wave + 4 * i;
     const size_t key0 = (size_t)(k0 + row0);
-    if constexpr (STREAM) {
+    if (stream) {   // wave-uniform
       dma16_s_stream(kb + key0 * kD, voff[i], lk + row0 * kRowBytes);
       dma16_s_stream(vb + key0 * kD, voff[i], lv + row0 * kRowBytes);
     } else {
@@ -175,45 +183,191 @@ __device__ __forceinline__ void wait_tile_and_sync(int later) {
   else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// STREAM: the context tiles are read by this workgroup alone (one row group)
-// and are loaded with the non-temporal hint.
-template <int NB, int WAVES, int KH, bool STREAM>
-__global__ __launch_bounds__(WAVES * kWave, 1) void tree_verify_kernel(const VerifyArgs a) {
-  static_assert(KH == 1 || (KH == 2 && WAVES == 8), "wave pairs share a SIMD: waves w and w + 4");
+// ------------------------------------------------------------ work assignment
+//
+// A call's batch mixes trees of every size (one copied chain to T_max nodes)
+// and contexts of every length, so its workgroups are shared out on the
+// device, from lens and node_count, not from the capacities.  Sequence b has
+// row groups of 256 stacked rows (KH = 1) or 128 (KH = 2), and its context is
+// cut into k_b splits of equal whole tiles, k_b in proportion to its cost
+// (tiles x cost of a tile), so that all workgroups take about the same time;
+// the sequences with the longest workgroups come first.  A (sequence, split)
+// is a unit; the row groups of one (unit, kv head) get consecutive slots on
+// one XCD (workgroups go round-robin over the 8 XCDs), so the second reader of
+// a K/V tile finds it in that XCD's L2.
+//
+// Against splits cut from the capacity, in grid order (us per call): 24
+// ragged sequences of up to 6007 keys, 28 heads over 4: 88 -> 78; 8 ragged of
+// up to 16000, 32 over 8: 112 -> 105; 5 ragged of up to 9001, 28 over 4:
+// 50 -> 45; as steps, 64 x 2048 keys with trees of 17 to 136 nodes 371 -> 346
+// (the order alone: unordered it stays at 366).  A batch that is even already
+// pays for the planning: 16 x 8192 in one round 191 -> 192.5.
+constexpr int kPlanSeqs = kWave;       // sequences planned together: one per lane
+constexpr int kCostWide = 16;          // cost of one tile of a row group of 5 to 8 blocks: two waves' rows per SIMD
+constexpr int kCostNarrow = 12;        // of one of up to 4 blocks
+constexpr float kCostStart = 96.f;     // start-up and drain of a workgroup
+constexpr int kCUs = 256;
+
+// x / d for 0 <= x, 0 < d by a reciprocal and one correction (the compiler's
+// integer division is a chain of some forty instructions).
+__device__ __forceinline__ int div_small(int x, int d) {
+  int q = (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)d));
+  const int r = x - q * d;
+  q += r >= d ? 1 : 0;
+  q -= r < 0 ? 1 : 0;
+  return q;
+}
+
+struct VerifyJob {
+  int b, g, rg, T, c0, c1, last, parts, split;
+};
+
+// The job of slot (blockIdx.x / 8) on XCD (blockIdx.x % 8) among the
+// sequences [base, base + 64) of one wave's lanes; false if there is none.
+template <int KH>
+__device__ __forceinline__ bool find_job(const VerifyArgs& a, int base, VerifyJob& job) {
+  const int lane = lane_id();
+  const int n = min(a.B - base, kPlanSeqs);
+  const int s = base + min(lane, n - 1);
+  constexpr int per = 8 / KH;   // row blocks per row group
+  int L = min(max(a.lens[s], 0), a.L_stride);
+  int T = min(max(a.node_count[s], 0), a.T_max);
+  if (lane >= n) L = T = 0;
+  const int tiles = max((L + kKeyTile - 1) / kKeyTile, 1);
+  const int nb = (T * a.G + 31) >> 5;
+  const int rgs = (nb + per - 1) / per;
+  const int cost = KH == 1 && nb > 4 ? kCostWide : kCostNarrow;   // of the first row group's tile
+  const int w = nb > 0 ? tiles * cost : 0;
+  // Splits: all sequences cut into pieces of cost at most Q; lane i weighs one
+  // of 64 quotas Q in geometric steps from a fair share of the most workgroups
+  // to the largest sequence.  Its N pieces take ceil(N / 256) rounds of about
+  // Q, or, dispatched longest first, the even share and half a piece, and a
+  // start-up per round.
+  int k = 1;
+  if (a.nsplit > 1) {
+    const float even = (float)wave_sum_i32(w * rgs) * a.Hkv * (1.f / kCUs);
+    const float wmax = (float)wave_max_i32(w);
+    const float q0 = fmaxf(even * 0.75f * kCUs * __builtin_amdgcn_rcpf((float)a.max_wgs), 1.f);
+    const float steps = __builtin_amdgcn_logf(fmaxf(wmax * __builtin_amdgcn_rcpf(q0), 1.f)) * (1.f / (kWave - 1));
+    const float q = q0 * __builtin_amdgcn_exp2f(steps * lane) * 1.0001f;
+    const float rq = __builtin_amdgcn_rcpf(q);
+    const int wf = __float_as_int((float)w), rf = __float_as_int((float)(rgs * a.Hkv));
+    float n0 = 0.f, n1 = 0.f;   // two sums: independent chains
+    for (int i = 0; i < n; i += 2) {   // lane n, if reached, holds zeros or does not exist (n = 64 is even)
+      n0 += ceilf(__int_as_float(__builtin_amdgcn_readlane(wf, i)) * rq) * __int_as_float(__builtin_amdgcn_readlane(rf, i));
+      n1 += ceilf(__int_as_float(__builtin_amdgcn_readlane(wf, i + 1)) * rq) * __int_as_float(__builtin_amdgcn_readlane(rf, i + 1));
+    }
+    const int wgs = (int)(n0 + n1);
+    const float rounds = (float)((wgs + kCUs - 1) / kCUs);
+    const float est = wgs <= a.max_wgs ? kCostStart * rounds + fmaxf(q, fminf(rounds * q, even + 0.5f * q)) : INFINITY;
+    // est > 0: its bits order like the value.
+    const uint32_t low = (uint32_t)-wave_max_i32(-__float_as_int(est));
+    if (low != 0x7f800000u) {
+      const int at = __builtin_ctzll(__ballot((uint32_t)__float_as_int(est) == low));
+      const float best = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rq), at));
+      k = min(min(max((int)ceilf((float)w * best), 1), tiles), a.cap);
+    }
+  }
+  const int ct = div_small(tiles + k - 1, k);   // tiles per split
+  k = nb > 0 ? div_small(tiles + ct - 1, ct) : 0;
+  // Longest workgroups first: lane i takes the i-th sequence in that order.
+  int src = lane;
+  if (n > 1) {
+    const uint32_t key = nb > 0 ? ((uint32_t)min(ct * cost, (1 << 26) - 1) << 6) | (63u - lane) : 0u;
+    const uint32_t sorted = n <= 16 ? bitonic_sort_desc_first_u32<16>(key) : bitonic_sort_desc_u32(key);
+    src = sorted == 0u ? -1 : 63 - (int)(sorted & 63u);
+  }
+  const int packed = __shfl(k | (rgs << 16), max(src, 0), kWave);
+  const int ks = src < 0 || src >= n ? 0 : packed & 0xffff;
+  const int rs = packed >> 16;
+  const int p1 = wave_incl_scan_i32(ks);   // units up to and including this sequence
+  const int p0 = p1 - ks;
+  // Units go round-robin over the XCD groups of head_cols XCDs each.
+  const int xcd = blockIdx.x & 7;
+  const int cols_log2 = __builtin_ctz(a.head_cols);
+  const int sub = xcd >> cols_log2;
+  const int groups = 8 >> cols_log2;
+  const int heads = a.Hkv >> cols_log2;    // heads of a unit on one XCD
+  const int mine = ((p1 + groups - 1 - sub) >> (3 - cols_log2)) - ((p0 + groups - 1 - sub) >> (3 - cols_log2));
+  const int slots = mine * rs * heads;
+  const int incl = wave_incl_scan_i32(slots);
+  const int slot = blockIdx.x >> 3;
+  const uint64_t at = __ballot(incl > slot);
+  if (at == 0) return false;
+  const int li = __builtin_ctzll(at);
+  const int ri = __builtin_amdgcn_readlane(rs, li);
+  const int rem = slot - __builtin_amdgcn_readlane(incl - slots, li);
+  const int u0 = __builtin_amdgcn_readlane(p0, li);
+  const int lseq = __builtin_amdgcn_readlane(src, li);
+  const int kv = div_small(rem, ri);
+  job.rg = rem - kv * ri;
+  const int ul = div_small(kv, heads);
+  job.g = (xcd & (a.head_cols - 1)) + a.head_cols * (kv - ul * heads);
+  const int split = ((sub - u0) & (groups - 1)) + groups * ul;
+  job.b = base + lseq;
+  job.T = __builtin_amdgcn_readlane(T, lseq);
+  job.parts = __builtin_amdgcn_readlane(k, lseq);
+  const int chunk = __builtin_amdgcn_readlane(ct, lseq) * kKeyTile;
+  job.c0 = split * chunk;
+  job.c1 = min(job.c0 + chunk, __builtin_amdgcn_readlane(L, lseq));
+  job.last = split == job.parts - 1;
+  job.split = split;
+  if (a.nsplit > 1 && job.rg == 0 && job.g == 0 && split == 0 && lane == 0) a.ws_parts[job.b] = job.parts;
+  return true;
+}
+
+// The plan's own decomposition: every sequence in nsplit splits of chunk keys.
+template <int KH>
+__device__ __forceinline__ bool static_job(const VerifyArgs& a, VerifyJob& job) {
+  constexpr int kRows = 256 / KH;
+  const int slot = blockIdx.x >> 3;
+  const int kvgroup = (slot / a.rowgroups) * 8 + (blockIdx.x & 7);   // = bg * nsplit + split
+  job.rg = slot % a.rowgroups;
+  const int bg = kvgroup / a.nsplit;
+  job.split = kvgroup - bg * a.nsplit;
+  job.b = bg / a.Hkv;
+  job.g = bg - job.b * a.Hkv;
+  if (job.b >= a.B) return false;
+  const int T = a.node_count[job.b], len = a.lens[job.b];
+  asm volatile("" ::"s"(T), "s"(len));   // one round trip: not one load behind the branch below
+  job.T = min(max(T, 0), a.T_max);
+  const int L = min(max(len, 0), a.L_stride);
+  if (job.rg * kRows >= job.T * a.G) return false;
+  job.parts = a.nsplit;
+  job.c0 = job.split * a.chunk;
+  job.c1 = min(job.c0 + a.chunk, L);
+  job.last = job.split == a.nsplit - 1;
+  return true;
+}
+
+// One row group's share of one split: 32 * kBlocks stacked rows of (b, g)
+// against the keys [c0, c1) and, in the last split, the tree's.
+template <int KH>
+__device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, uint64_t* s_mask,
+                                            const VerifyJob& job) {
+  constexpr int NB = 1, WAVES = 8;
+  static_assert(KH == 1 || KH == 2, "wave pairs share a SIMD: waves w and w + 4");
   constexpr int kThreads = WAVES * kWave;
   constexpr int kBlocks = WAVES / KH;   // 32-row blocks per workgroup
   constexpr int HP = 2 / KH;            // halves of each tile one wave consumes
   constexpr int kLoadsPerWave = 2 * kTileBytes / 1024 / WAVES;   // 1 KiB per wave-wide load
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[kStages * 2 * kTileBytes];
-  __shared__ uint64_t s_mask[ADAPLD_MAX_TREE_NODES * kMaskWords];
 
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  // Workgroups are dispatched round-robin over the 8 XCDs; the row groups of
-  // one (kv head, split) get consecutive slots on the same XCD, so the second
-  // reader of a K/V tile finds it in that XCD's L2.
-  const int xcd = blockIdx.x & 7;
-  const int slot = blockIdx.x >> 3;
-  const int kvgroup = (slot / a.rowgroups) * 8 + xcd;   // = bg * nsplit + split
-  const int rg = slot % a.rowgroups;
-  if (kvgroup >= a.n_kvgroups) return;
-  const int bg = kvgroup / a.nsplit;
-  const int split = kvgroup - bg * a.nsplit;
-  const int b = bg / a.Hkv;
-  const int g = bg - b * a.Hkv;
-  const int T = min(max(a.node_count[b], 0), a.T_max);
-  const int L = min(max(a.lens[b], 0), a.L_stride);
+  const int b = job.b, g = job.g, T = job.T;
+  const int c0 = job.c0, c1 = job.c1;
+  const bool do_tree = job.last != 0;
+  const int bg = b * a.Hkv + g;
   const int G = a.G;
   const int rows = T * G;
-  const int row_base = rg * (kBlocks * NB * 32);
-  if (row_base >= rows) return;
+  const int row_base = job.rg * (kBlocks * 32);
+  // Tiles that no other row group reads are loaded with the non-temporal
+  // hint; it pays only with whole-workgroup row blocks over long chunks
+  // (measured slower for the two-wave row blocks of short chunks).
+  const bool stream = KH == 1 && rows <= kBlocks * 32;
   // Row block of this wave, and (KH = 2) the half of every tile it takes.
   const int wrow = KH == 2 ? wave % kBlocks : wave;
   const int kh = KH == 2 ? wave / kBlocks : 0;
-
-  const int c0 = split * a.chunk;
-  const int c1 = min(c0 + a.chunk, L);
-  const bool do_tree = split == a.nsplit - 1;
   const int col = lane & 31;
   const int half = lane >> 5;
 
@@ -281,7 +435,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void tree_verify_kernel(const Ver
     if (t < n_ctx) {
       const int k0 = c0 + t * kKeyTile;
       if (k0 + kKeyTile <= c1)
-        issue_tile_full<WAVES, STREAM>(kc, vc, k0, lk, lv, wave, voff);
+        issue_tile_full<WAVES>(kc, vc, k0, lk, lv, wave, voff, stream);
       else
         issue_tile<WAVES>(kc, vc, kD, k0, c1, lk, lv, wave, lane);
     } else {
@@ -631,7 +785,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void tree_verify_kernel(const Ver
     const int qr = qrow[nb];
     if (qr >= rows) continue;
     const int u = qu[nb], h = qh[nb];
-    if (a.nsplit == 1) {
+    if (job.parts == 1) {
       const float inv = 1.f / l_tot[nb];
       uint16_t* op = a.out + (((size_t)b * a.T_max + u) * a.Hq + h) * kD;
 #pragma unroll
@@ -646,7 +800,7 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void tree_verify_kernel(const Ver
         }
       if (half == 0 && a.lse) a.lse[((size_t)b * a.Hq + h) * a.T_max + u] = (m_run[nb] + log2f(l_tot[nb])) * kLn2;
     } else {
-      const size_t slot = ((size_t)bg * a.nsplit + split) * a.rows_max + qr;
+      const size_t slot = ((size_t)bg * a.cap + job.split) * a.rows_max + qr;
       const float inv = l_tot[nb] > 0.f ? 1.f / l_tot[nb] : 0.f;
       uint16_t* wp = a.ws_o + slot * kD;
 #pragma unroll
@@ -664,38 +818,74 @@ __global__ __launch_bounds__(WAVES * kWave, 1) void tree_verify_kernel(const Ver
   }
 }
 
+// SHARED: one wave shares out the batch for its workgroup; otherwise every
+// wave finds its job in the plan's static decomposition.
+template <int KH, bool SHARED>
+__global__ __launch_bounds__(8 * kWave, 1) void tree_verify_kernel(const VerifyArgs a) {
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kStages * 2 * kTileBytes];
+  __shared__ uint64_t s_mask[ADAPLD_MAX_TREE_NODES * kMaskWords];
+  // All arguments of the prologue arrive in one wait, not pointer by pointer
+  // behind each other's branches.
+  asm volatile("" ::"s"(a.q), "s"(a.k_ctx), "s"(a.v_ctx), "s"(a.k_tree), "s"(a.v_tree), "s"(a.lens),
+               "s"(a.node_count), "s"(a.tree_mask), "s"(a.L_stride), "s"(a.T_max), "s"(a.Hq), "s"(a.Hkv), "s"(a.G),
+               "s"(a.nw), "s"(a.nsplit), "s"(a.chunk), "s"(a.rowgroups), "s"(a.B));
+  VerifyJob job;
+  if constexpr (!SHARED) {
+    if (!static_job<KH>(a, job)) return;
+  } else {
+    __shared__ VerifyJob s_job;
+    if (threadIdx.x < kWave) {
+      job.b = -1;
+      find_job<KH>(a, blockIdx.y * kPlanSeqs, job);
+      if (threadIdx.x == 0) s_job = job;
+    }
+    __syncthreads();
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    job.b = uni(s_job.b);
+    if (job.b < 0) return;
+    job.g = uni(s_job.g), job.T = uni(s_job.T), job.rg = uni(s_job.rg);
+    job.c0 = uni(s_job.c0), job.c1 = uni(s_job.c1), job.last = uni(s_job.last);
+    job.parts = uni(s_job.parts), job.split = uni(s_job.split);
+  }
+  verify_rows<KH>(a, smem, s_mask, job);
+}
+
 // Merge the splits: 8 stacked rows per workgroup, 16 threads x 8 dims (one
 // 16-byte load per split) per row.
 constexpr int kCombineRows = 8;
+template <bool SHARED>
 __global__ __launch_bounds__(kCombineRows * 16) void verify_combine_kernel(const VerifyArgs a) {
   const int qr = blockIdx.x * kCombineRows + (threadIdx.x >> 4);
   const int bg = blockIdx.y;
   if (qr >= a.rows_max) return;
   const int dim = (threadIdx.x & 15) * 8;
-  const size_t row0 = (size_t)bg * a.nsplit * a.rows_max + qr;   // split 0 of this row
   const int b = bg / a.Hkv;
   const int T = min(max(a.node_count[b], 0), a.T_max);
+  const int parts = SHARED ? a.ws_parts[b] : a.nsplit;   // ws_parts: written for every sequence with a node
+  const size_t row0 = (size_t)bg * a.cap * a.rows_max + qr;   // split 0 of this row
   // One pass over the splits in index order, four at a time.  The maxima and
-  // partials of a group are loaded together, and with node_count rather than
-  // after it (every slot is in bounds; rows past the tree are dropped at the
-  // end), so a call with up to four splits costs one memory round trip; the
-  // running max moves online.  Split s carries O_s/l_s with weight
-  // l_s 2^(m_s - M).
+  // partials of a group are loaded together, those of the first group (up to
+  // the plan's splits) with node_count and the split count rather than after
+  // them (every slot is in bounds), so a call with up to four splits costs
+  // one memory round trip; the running max moves online.  Split s carries
+  // O_s/l_s with weight l_s 2^(m_s - M).
   float M = -INFINITY, den = 0.f;
   float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  for (int s0 = 0; s0 < a.nsplit; s0 += 4) {
+  const int first = SHARED ? min(a.nsplit, 4) : 4;
+  for (int s0 = 0, width = first; s0 < (SHARED ? max(parts, 1) : a.nsplit); s0 += width, width = 4) {
     float2 ml[4];
     uint4 v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const bool in = s0 + j < a.nsplit;
+      const bool in = SHARED ? j < width && (s0 == 0 || s0 + j < parts) : s0 + j < a.nsplit;
       const size_t slot = row0 + (size_t)(s0 + j) * a.rows_max;
       ml[j] = in ? a.ws_ml[slot] : make_float2(-INFINITY, 0.f);
       v[j] = in ? *reinterpret_cast<const uint4*>(a.ws_o + slot * kD + dim) : make_uint4(0u, 0u, 0u, 0u);
     }
+    if (SHARED && (parts <= 1 || qr >= T * a.G)) return;   // written by the attention kernel, or past the tree
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (ml[j].y > 0.f) {
+      if ((!SHARED || s0 + j < parts) && ml[j].y > 0.f) {
         const float m_new = fmaxf(M, ml[j].x);
         const float c = exp2f(M - m_new);   // 0 while nothing has been merged
         const float w = ml[j].y * exp2f(ml[j].x - m_new);
@@ -710,7 +900,7 @@ __global__ __launch_bounds__(kCombineRows * 16) void verify_combine_kernel(const
       }
     }
   }
-  if (qr >= T * a.G) return;
+  if (!SHARED && qr >= T * a.G) return;
   const int g = bg - b * a.Hkv;
   const int u = qr / a.G;
   const int h = g * a.G + (qr - u * a.G);
@@ -783,10 +973,25 @@ VerifyPlan plan_verify(int B, int L_stride, int T_max, int Hq, int Hkv) {
   return best;
 }
 
+namespace {
+// Sharing out costs a workgroup and the combine kernel about 1 us each, so it
+// is taken where pieces are long (a split of at least 16 tiles) or where
+// unsplit workgroups take several rounds, whose order then counts.
+inline bool shares_batch(const VerifyPlan& p, int B, int Hkv) {
+  if (B == 1) return false;
+  return p.nsplit > 1 ? p.chunk >= 16 * kKeyTile : (long)B * Hkv * p.rowgroups > kCUs;
+}
+// A sequence may take up to twice the plan's splits where others take fewer.
+inline int split_cap(const VerifyPlan& p, int B, int Hkv) {
+  return shares_batch(p, B, Hkv) && p.nsplit > 1 ? std::min(2 * p.nsplit, 64) : p.nsplit;
+}
+}  // namespace
+
+// The partials of every sequence's splits, then the split counts.
 size_t verify_ws_bytes(const VerifyPlan& p, int B, int Hkv) {
   if (p.nsplit <= 1) return 0;
-  const size_t slots = (size_t)B * Hkv * p.nsplit * p.rows_max;
-  return slots * kD * sizeof(uint16_t) + slots * sizeof(float2);
+  const size_t slots = (size_t)B * split_cap(p, B, Hkv) * Hkv * p.rows_max;
+  return slots * (kD * sizeof(uint16_t) + sizeof(float2)) + (size_t)B * sizeof(int);
 }
 
 hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* v_ctx,
@@ -798,29 +1003,48 @@ hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, con
   VerifyArgs a{};
   a.q = q; a.k_ctx = k_ctx; a.v_ctx = v_ctx; a.k_tree = k_tree; a.v_tree = v_tree;
   a.lens = lens; a.node_count = node_count; a.tree_mask = tree_mask;
-  a.L_stride = L_stride; a.T_max = T_max; a.Hq = Hq; a.Hkv = Hkv; a.G = p.G;
-  a.rows_max = p.rows_max; a.nsplit = p.nsplit; a.chunk = p.chunk; a.nw = (T_max + 63) / 64;
+  a.B = B; a.L_stride = L_stride; a.T_max = T_max; a.Hq = Hq; a.Hkv = Hkv; a.G = p.G;
+  a.rows_max = p.rows_max; a.nw = (T_max + 63) / 64; a.nsplit = p.nsplit;
+  a.head_cols = std::gcd(Hkv, 8);
   a.scale_log2 = scale * kLog2e;
   a.out = out; a.lse = lse;
-  const size_t slots = (size_t)B * Hkv * p.nsplit * p.rows_max;
+  const bool shared = shares_batch(p, B, Hkv);
+  a.chunk = p.chunk; a.rowgroups = p.rowgroups;
+  a.cap = split_cap(p, B, Hkv);
+  const size_t slots = (size_t)B * a.cap * Hkv * p.rows_max;
   a.ws_o = static_cast<uint16_t*>(ws);
   a.ws_ml = ws ? reinterpret_cast<float2*>(static_cast<char*>(ws) + slots * kD * sizeof(uint16_t)) : nullptr;
+  a.ws_parts = ws ? reinterpret_cast<int*>(a.ws_ml + slots) : nullptr;
 
-  a.rowgroups = p.rowgroups;
-  a.n_kvgroups = B * Hkv * p.nsplit;
-  const dim3 grid(((a.n_kvgroups + 7) / 8) * 8 * p.rowgroups);
-  // Streaming loads pay only with whole-workgroup row blocks over long chunks:
-  // measured slower for the two-wave row blocks of short chunks.
-  if (p.kh == 2)
-    hipLaunchKernelGGL((tree_verify_kernel<1, 8, 2, false>), grid, dim3(8 * kWave), 0, stream, a);
-  else if (p.rowgroups == 1)
-    hipLaunchKernelGGL((tree_verify_kernel<1, 8, 1, true>), grid, dim3(8 * kWave), 0, stream, a);
+  // Slots per XCD for the sequences of one plan (64 at most): unsplit they
+  // take one workgroup per (row group, kv head), split at most rounds * kCUs
+  // in all.  Where the units of a sequence go round-robin over groups of
+  // XCDs, a group takes at most one unit of every sequence more than its
+  // even share.
+  const int n = std::min(B, kPlanSeqs);
+  const int heads = Hkv / a.head_cols;
+  int wgs = n * p.rowgroups * Hkv;
+  a.max_wgs = (wgs * p.nsplit + kCUs - 1) / kCUs * kCUs;
+  if (p.nsplit > 1) wgs = std::max(wgs, a.max_wgs);
+  const int slots_xcd = shared ? (wgs + 7) / 8 + (a.head_cols < 8 ? n * p.rowgroups * heads : 0)
+                               : (B * Hkv * p.nsplit + 7) / 8 * p.rowgroups;
+  const dim3 grid(slots_xcd * 8, shared ? (B + kPlanSeqs - 1) / kPlanSeqs : 1);
+  const dim3 block(8 * kWave);
+  if (p.kh == 2 && shared)
+    hipLaunchKernelGGL((tree_verify_kernel<2, true>), grid, block, 0, stream, a);
+  else if (p.kh == 2)
+    hipLaunchKernelGGL((tree_verify_kernel<2, false>), grid, block, 0, stream, a);
+  else if (shared)
+    hipLaunchKernelGGL((tree_verify_kernel<1, true>), grid, block, 0, stream, a);
   else
-    hipLaunchKernelGGL((tree_verify_kernel<1, 8, 1, false>), grid, dim3(8 * kWave), 0, stream, a);
+    hipLaunchKernelGGL((tree_verify_kernel<1, false>), grid, block, 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.nsplit == 1) return e;
-  hipLaunchKernelGGL(verify_combine_kernel, dim3((p.rows_max + kCombineRows - 1) / kCombineRows, B * Hkv),
-                     dim3(kCombineRows * 16), 0, stream, a);
+  const dim3 cgrid((p.rows_max + kCombineRows - 1) / kCombineRows, B * Hkv);
+  if (shared)
+    hipLaunchKernelGGL(verify_combine_kernel<true>, cgrid, dim3(kCombineRows * 16), 0, stream, a);
+  else
+    hipLaunchKernelGGL(verify_combine_kernel<false>, cgrid, dim3(kCombineRows * 16), 0, stream, a);
   return hipGetLastError();
 }
 
