@@ -170,3 +170,30 @@ def test_index_build_sizes(L, n_max):
     lens += rng.integers(0, 70, 8).astype(np.int32)
     lens_d.copy_(torch.from_numpy(lens))
     check(idx, tok, lens, tok_d, lens_d, n_max, "append", fused=True)
+
+
+@pytest.mark.parametrize("n_max", [1, 4, 16])
+@pytest.mark.parametrize("m", [0, 1, 16, 17, 63, 64, 65, 130])
+def test_index_lookup_beside_insertions(m, n_max):
+    """append_match of m new tokens at once (whole and broken batches of 64):
+    the last n-gram is absent from the batch, repeats inside it at every
+    level, is one of many equal ones, or is new altogether."""
+    B, L0 = 5, 400
+    cap = L0 + 2 * m + 8
+    rng = np.random.default_rng(100 * m + n_max)
+    tok = rng.integers(0, 60, size=(B, cap)).astype(np.int32)
+    lens = np.full(B, L0, np.int32)
+    tok_d, lens_d = torch.from_numpy(tok).cuda(), torch.from_numpy(lens).cuda()
+    idx = adapld.NgramIndex(B, cap, n_max).build(tok_d, lens_d)
+    for step in range(2):
+        lo = int(lens[0])
+        hi = lo + m
+        if m:
+            tok[0, lo:hi] = tok[0, 50:50 + m]                        # a copy of the context
+            tok[1, lo:hi] = np.resize(tok[1, lo - 3:lo], m)           # period 3: repeats inside the batch
+            tok[2, lo:hi] = 9                                         # one token over and over
+            tok[3, hi - 1] = 500 + step                               # ends on a new token
+        lens[:] = hi
+        tok_d.copy_(torch.from_numpy(tok))
+        lens_d.copy_(torch.from_numpy(lens))
+        check(idx, tok, lens, tok_d, lens_d, n_max, f"m={m} step {step}", fused=True)
