@@ -92,6 +92,7 @@ struct VerifyArgs {
   int chunk, rowgroups;   // context keys per split and row groups in the plan
   int cap;         // most splits of one sequence (its slots in the workspace)
   int max_wgs;     // workgroups that a split batch may take
+  int stream;      // nonzero: tiles that one workgroup reads are loaded with the non-temporal hint
   int head_cols;   // XCDs that the heads of one (sequence, split) unit spread over: gcd(Hkv, 8)
   float scale_log2;
   uint16_t* out;
@@ -141,8 +142,9 @@ __device__ __forceinline__ void dma16_s(const void* gbase, uint32_t voff, uint32
                : "memory", "m0");
 }
 // The same with the non-temporal hint, for tiles that no other workgroup
-// reads (one row group): the caches treat them as streaming.  With two or
-// more row groups the tiles must stay in L2 for the other readers.
+// reads (one row group) of a K/V cache too large for the last-level cache: the
+// caches then treat them as streaming.  With two or more row groups the tiles
+// must stay in L2 for the other readers.
 __device__ __forceinline__ void dma16_s_stream(const void* gbase, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                :
@@ -361,10 +363,7 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
   const int G = a.G;
   const int rows = T * G;
   const int row_base = job.rg * (kBlocks * 32);
-  // Tiles that no other row group reads are loaded with the non-temporal
-  // hint; it pays only with whole-workgroup row blocks over long chunks
-  // (measured slower for the two-wave row blocks of short chunks).
-  const bool stream = KH == 1 && rows <= kBlocks * 32;
+  const bool stream = a.stream && rows <= kBlocks * 32;   // no other row group reads these tiles
   // Row block of this wave, and (KH = 2) the half of every tile it takes.
   const int wrow = KH == 2 ? wave % kBlocks : wave;
   const int kh = KH == 2 ? wave / kBlocks : 0;
@@ -1010,6 +1009,15 @@ hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, con
   a.out = out; a.lse = lse;
   const bool shared = shares_batch(p, B, Hkv);
   a.chunk = p.chunk; a.rowgroups = p.rowgroups;
+  // K and V that fit the 256 MiB last-level cache may be found there by the
+  // next call, which streaming loads give up; beyond it the hint pays, with
+  // both shapes (us per call, plain / non-temporal loads): 32 x 4096 keys, 32
+  // heads over 8 104.4 / 87.0, 12 x 20000, 16 over 16 253 / 230, 10 x 9876, 40
+  // over 8 80.8 / 71.3, 4 x 32768, 32 over 32 374 / 316, 24 x 4096 75.2 / 63.9;
+  // at 256 MiB 64 x 1024 53.5 / 57.4 and 2 x 32768 54.1 / 56.3, below it 8 x
+  // 4096 41.9 / 44.2 with 52-node trees and 32.0 / 31.7 with 16-node ones.
+  constexpr size_t kCacheBytes = (size_t)256 << 20;
+  a.stream = (size_t)B * L_stride * Hkv * 2 * kRowBytes > kCacheBytes;
   a.cap = split_cap(p, B, Hkv);
   const size_t slots = (size_t)B * a.cap * Hkv * p.rows_max;
   a.ws_o = static_cast<uint16_t*>(ws);
