@@ -142,8 +142,8 @@ __device__ __forceinline__ void dma16_s(const void* gbase, uint32_t voff, uint32
                : "memory", "m0");
 }
 // The same with the non-temporal hint, for tiles that no other workgroup
-// reads (one row group) of a K/V cache too large for the last-level cache: the
-// caches then treat them as streaming.  With two or more row groups the tiles
+// reads (one row group): the caches then treat them as streaming.  With two or
+// more row groups the tiles
 // must stay in L2 for the other readers.
 __device__ __forceinline__ void dma16_s_stream(const void* gbase, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(kCombineRows * 16) void verify_combine_kernel(const
   const int dim = (threadIdx.x & 15) * 8;
   const int b = bg / a.Hkv;
   const int T = min(max(a.node_count[b], 0), a.T_max);
-  const int parts = SHARED ? a.ws_parts[b] : a.nsplit;   // ws_parts: written for every sequence with a node
+  const int parts = SHARED ? min(a.ws_parts[b], a.cap) : a.nsplit;   // written for every sequence with a node
   const size_t row0 = (size_t)bg * a.cap * a.rows_max + qr;   // split 0 of this row
   // One pass over the splits in index order, four at a time.  The maxima and
   // partials of a group are loaded together, those of the first group (up to
@@ -1009,15 +1009,17 @@ hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, con
   a.out = out; a.lse = lse;
   const bool shared = shares_batch(p, B, Hkv);
   a.chunk = p.chunk; a.rowgroups = p.rowgroups;
-  // K and V that fit the 256 MiB last-level cache may be found there by the
-  // next call, which streaming loads give up; beyond it the hint pays, with
-  // both shapes (us per call, plain / non-temporal loads): 32 x 4096 keys, 32
-  // heads over 8 104.4 / 87.0, 12 x 20000, 16 over 16 253 / 230, 10 x 9876, 40
-  // over 8 80.8 / 71.3, 4 x 32768, 32 over 32 374 / 316, 24 x 4096 75.2 / 63.9;
-  // at 256 MiB 64 x 1024 53.5 / 57.4 and 2 x 32768 54.1 / 56.3, below it 8 x
-  // 4096 41.9 / 44.2 with 52-node trees and 32.0 / 31.7 with 16-node ones.
-  constexpr size_t kCacheBytes = (size_t)256 << 20;
-  a.stream = (size_t)B * L_stride * Hkv * 2 * kRowBytes > kCacheBytes;
+  // A model's layers each bring their own K and V, so a call finds them in
+  // HBM, not in the 256 MiB last-level cache; streaming loads then pay for
+  // either shape (us per call over rotating inputs of over 1 GB, plain /
+  // non-temporal): 32 heads over 8, 16 nodes: 2 x 4096 keys 21.3 / 20.8, 4 x
+  // 25.0 / 23.6, 8 x 37.6 / 33.9, 16 x 59.5 / 53.4, 24 x 76.1 / 66.4, 1 x 32768
+  // 40.1 / 37.5; 52 nodes, 8 x 4096 48.3 / 46.3; 16 over 16, 12 x 4096 66.7 /
+  // 59.4.  Called again on the same K and V, up to 256 MiB stay in that cache
+  // and plain loads win where the call is small: 3 x 3000 19.9 / 21.5, 1 x 2000
+  // 16.6 / 17.0, but 4 x 4096 22.8 / 22.1.  So small caches load plainly.
+  constexpr size_t kPlainBytes = (size_t)64 << 20;
+  a.stream = (size_t)B * L_stride * Hkv * 2 * kRowBytes >= kPlainBytes;
   a.cap = split_cap(p, B, Hkv);
   const size_t slots = (size_t)B * a.cap * Hkv * p.rows_max;
   a.ws_o = static_cast<uint16_t*>(ws);
