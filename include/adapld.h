@@ -121,10 +121,10 @@ size_t adapld_workspace_bytes(int op, int B, int L_stride, int d, int k, int T_m
  * key tile), info[2] stacked rows per workgroup, info[3] workgroups per
  * (sequence, kv head) along the rows, info[4] context splits (the partials
  * of more than one are merged by a second kernel), info[5] context keys per
- * split.  In a batch of long splits or of several rounds of workgroups, the
- * call shares these workgroups out by the sequences' lengths and node counts:
- * info[4] is then the splits per sequence on average, and one sequence takes
- * at most twice as many.  `info` is host memory of at least 6 ints, owned by the caller.
+ * split.  The context is cut at the same keys whatever the batch holds: a
+ * sequence's results depend on its own inputs and these sizes alone, not on
+ * its batch-mates, which decide only the order in which workgroups run.
+ * `info` is host memory of at least 6 ints, owned by the caller.
  * Returns ADAPLD_OK, ADAPLD_ERR_NULL_ARG, or ADAPLD_ERR_INVALID_ARG /
  * ADAPLD_ERR_UNSUPPORTED for sizes the entry point itself would reject. */
 int adapld_verify_plan(int B, int L_stride, int T_max, int Hq, int Hkv, int32_t* info);

@@ -88,18 +88,16 @@ struct VerifyArgs {
   const int32_t* node_count;
   const uint64_t* tree_mask;
   int B, L_stride, T_max, Hq, Hkv, G, rows_max, nw;
-  int nsplit;      // splits per sequence in the plan (1: no sequence is split)
-  int chunk, rowgroups;   // context keys per split and row groups in the plan
-  int cap;         // most splits of one sequence (its slots in the workspace)
-  int max_wgs;     // workgroups that a split batch may take
+  int nsplit;      // splits per sequence (1: no sequence is split)
+  int chunk, rowgroups;   // context keys per split, row groups of a full tree
+  int plan_seqs;   // sequences that one plan orders
   int stream;      // nonzero: tiles that one workgroup reads are loaded with the non-temporal hint
   int head_cols;   // XCDs that the heads of one (sequence, split) unit spread over: gcd(Hkv, 8)
   float scale_log2;
   uint16_t* out;
   float* lse;
-  uint16_t* ws_o;  // [B*Hkv][cap][rows_max][D]  partial outputs O/l, bf16
-  float2* ws_ml;   // [B*Hkv][cap][rows_max]     (running max in log2 units, sum)
-  int* ws_parts;   // [B]  splits of every sequence
+  uint16_t* ws_o;  // [B*Hkv][nsplit][rows_max][D]  partial outputs O/l, bf16
+  float2* ws_ml;   // [B*Hkv][nsplit][rows_max]     (running max in log2 units, sum)
 };
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
@@ -187,31 +185,27 @@ __device__ __forceinline__ void wait_tile_and_sync(int later) {
 
 // ------------------------------------------------------------ work assignment
 //
-// A call's batch mixes trees of every size (one copied chain to T_max nodes)
-// and contexts of every length, so its workgroups are shared out on the
-// device, from lens and node_count, not from the capacities.  Sequence b has
-// row groups of 256 stacked rows (KH = 1) or 128 (KH = 2), and its context is
-// cut into k_b splits of equal whole tiles, k_b in proportion to its cost
-// (tiles x cost of a tile), so that all workgroups take about the same time;
-// the sequences with the longest workgroups come first.  A (sequence, split)
-// is a unit; the row groups of one (unit, kv head) get consecutive slots on
-// one XCD (workgroups go round-robin over the 8 XCDs), so the second reader of
-// a K/V tile finds it in that XCD's L2.
+// Every context is cut at the same keys whatever the batch holds: split s of
+// the plan's nsplit takes the keys [s * chunk, (s + 1) * chunk), the last one
+// also the tree's, so a sequence's results follow from its own inputs and the
+// shape arguments alone.  A piece is a split with a key or a tree to read; a
+// (sequence, piece) is a unit of up to rowgroups workgroups per kv head.
 //
-// Against splits cut from the capacity, in grid order (us per call): 24
-// ragged sequences of up to 6007 keys, 28 heads over 4: 88 -> 78; 8 ragged of
-// up to 16000, 32 over 8: 112 -> 105; 5 ragged of up to 9001, 28 over 4:
-// 50 -> 45; as steps, 64 x 2048 keys with trees of 17 to 136 nodes 371 -> 346
-// (the order alone: unordered it stays at 366).  A batch that is even already
-// pays for the planning: 16 x 8192 in one round 191 -> 192.5.
-constexpr int kPlanSeqs = kWave;       // sequences planned together: one per lane
+// A call's batch mixes trees of every size (one copied chain to T_max nodes)
+// and contexts of every length.  Where its workgroups take several rounds over
+// the CUs, they are dispatched longest first, shared out on the device from
+// lens and node_count: only pieces get workgroups, the sequences with the
+// longest pieces come first, and the row groups of one (unit, kv head) get
+// consecutive slots on one XCD (workgroups go round-robin over the 8 XCDs), so
+// the second reader of a K/V tile finds it in that XCD's L2.
+constexpr int kPlanSeqs = kWave;       // most sequences ordered together: one per lane
 constexpr int kCostWide = 16;          // cost of one tile of a row group of 5 to 8 blocks: two waves' rows per SIMD
 constexpr int kCostNarrow = 12;        // of one of up to 4 blocks
-constexpr float kCostStart = 96.f;     // start-up and drain of a workgroup
 constexpr int kCUs = 256;
 
 // x / d for 0 <= x, 0 < d by a reciprocal and one correction (the compiler's
-// integer division is a chain of some forty instructions).
+// integer division is a chain of some forty instructions).  Exact for
+// quotients below 2^22.
 __device__ __forceinline__ int div_small(int x, int d) {
   int q = (int)(((float)x + 0.5f) * __builtin_amdgcn_rcpf((float)d));
   const int r = x - q * d;
@@ -221,61 +215,36 @@ __device__ __forceinline__ int div_small(int x, int d) {
 }
 
 struct VerifyJob {
-  int b, g, rg, T, c0, c1, last, parts, split;
+  int b, g, rg, T, c0, c1, split;
 };
 
+// Splits of a context of L keys that hold a key: [0, this).
+__device__ __forceinline__ int splits_with_keys(const VerifyArgs& a, int L) {
+  return L > 0 ? div_small(L - 1, a.chunk) + 1 : 0;
+}
+
 // The job of slot (blockIdx.x / 8) on XCD (blockIdx.x % 8) among the
-// sequences [base, base + 64) of one wave's lanes; false if there is none.
+// sequences [base, base + plan_seqs) of one wave's lanes; false if there is none.
 template <int KH>
 __device__ __forceinline__ bool find_job(const VerifyArgs& a, int base, VerifyJob& job) {
   const int lane = lane_id();
-  const int n = min(a.B - base, kPlanSeqs);
+  const int n = min(a.B - base, a.plan_seqs);
   const int s = base + min(lane, n - 1);
   constexpr int per = 8 / KH;   // row blocks per row group
   int L = min(max(a.lens[s], 0), a.L_stride);
   int T = min(max(a.node_count[s], 0), a.T_max);
   if (lane >= n) L = T = 0;
-  const int tiles = max((L + kKeyTile - 1) / kKeyTile, 1);
   const int nb = (T * a.G + 31) >> 5;
   const int rgs = (nb + per - 1) / per;
-  const int cost = KH == 1 && nb > 4 ? kCostWide : kCostNarrow;   // of the first row group's tile
-  const int w = nb > 0 ? tiles * cost : 0;
-  // Splits: all sequences cut into pieces of cost at most Q; lane i weighs one
-  // of 64 quotas Q in geometric steps from a fair share of the most workgroups
-  // to the largest sequence.  Its N pieces take ceil(N / 256) rounds of about
-  // Q, or, dispatched longest first, the even share and half a piece, and a
-  // start-up per round.
-  int k = 1;
-  if (a.nsplit > 1) {
-    const float even = (float)wave_sum_i32(w * rgs) * a.Hkv * (1.f / kCUs);
-    const float wmax = (float)wave_max_i32(w);
-    const float q0 = fmaxf(even * 0.75f * kCUs * __builtin_amdgcn_rcpf((float)a.max_wgs), 1.f);
-    const float steps = __builtin_amdgcn_logf(fmaxf(wmax * __builtin_amdgcn_rcpf(q0), 1.f)) * (1.f / (kWave - 1));
-    const float q = q0 * __builtin_amdgcn_exp2f(steps * lane) * 1.0001f;
-    const float rq = __builtin_amdgcn_rcpf(q);
-    const int wf = __float_as_int((float)w), rf = __float_as_int((float)(rgs * a.Hkv));
-    float n0 = 0.f, n1 = 0.f;   // two sums: independent chains
-    for (int i = 0; i < n; i += 2) {   // lane n, if reached, holds zeros or does not exist (n = 64 is even)
-      n0 += ceilf(__int_as_float(__builtin_amdgcn_readlane(wf, i)) * rq) * __int_as_float(__builtin_amdgcn_readlane(rf, i));
-      n1 += ceilf(__int_as_float(__builtin_amdgcn_readlane(wf, i + 1)) * rq) * __int_as_float(__builtin_amdgcn_readlane(rf, i + 1));
-    }
-    const int wgs = (int)(n0 + n1);
-    const float rounds = (float)((wgs + kCUs - 1) / kCUs);
-    const float est = wgs <= a.max_wgs ? kCostStart * rounds + fmaxf(q, fminf(rounds * q, even + 0.5f * q)) : INFINITY;
-    // est > 0: its bits order like the value.
-    const uint32_t low = (uint32_t)-wave_max_i32(-__float_as_int(est));
-    if (low != 0x7f800000u) {
-      const int at = __builtin_ctzll(__ballot((uint32_t)__float_as_int(est) == low));
-      const float best = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(rq), at));
-      k = min(min(max((int)ceilf((float)w * best), 1), tiles), a.cap);
-    }
-  }
-  const int ct = div_small(tiles + k - 1, k);   // tiles per split
-  k = nb > 0 ? div_small(tiles + ct - 1, ct) : 0;
+  const int k = nb > 0 ? min(splits_with_keys(a, L) + 1, a.nsplit) : 0;   // with the last split
   // Longest workgroups first: lane i takes the i-th sequence in that order.
+  const int tiles = max((min(L, a.chunk) + kKeyTile - 1) / kKeyTile, 1);
+  const int cost = KH == 1 && nb > 4 ? kCostWide : kCostNarrow;   // of the first row group's tile
+  const uint32_t len = nb > 0 ? (uint32_t)min(tiles * cost, (1 << 26) - 1) : 0u;
   int src = lane;
-  if (n > 1) {
-    const uint32_t key = nb > 0 ? ((uint32_t)min(ct * cost, (1 << 26) - 1) << 6) | (63u - lane) : 0u;
+  // A batch of equal sequences is in order already.
+  if (__ballot(lane < n && len != (uint32_t)__builtin_amdgcn_readfirstlane(len)) != 0ull) {
+    const uint32_t key = len > 0u ? (len << 6) | (63u - lane) : 0u;
     const uint32_t sorted = n <= 16 ? bitonic_sort_desc_first_u32<16>(key) : bitonic_sort_desc_u32(key);
     src = sorted == 0u ? -1 : 63 - (int)(sorted & 63u);
   }
@@ -305,20 +274,17 @@ __device__ __forceinline__ bool find_job(const VerifyArgs& a, int base, VerifyJo
   job.rg = rem - kv * ri;
   const int ul = div_small(kv, heads);
   job.g = (xcd & (a.head_cols - 1)) + a.head_cols * (kv - ul * heads);
-  const int split = ((sub - u0) & (groups - 1)) + groups * ul;
+  const int piece = ((sub - u0) & (groups - 1)) + groups * ul;
   job.b = base + lseq;
   job.T = __builtin_amdgcn_readlane(T, lseq);
-  job.parts = __builtin_amdgcn_readlane(k, lseq);
-  const int chunk = __builtin_amdgcn_readlane(ct, lseq) * kKeyTile;
-  job.c0 = split * chunk;
-  job.c1 = min(job.c0 + chunk, __builtin_amdgcn_readlane(L, lseq));
-  job.last = split == job.parts - 1;
-  job.split = split;
-  if (a.nsplit > 1 && job.rg == 0 && job.g == 0 && split == 0 && lane == 0) a.ws_parts[job.b] = job.parts;
+  // the pieces are the splits with a key, then the last split
+  job.split = piece == __builtin_amdgcn_readlane(k, lseq) - 1 ? a.nsplit - 1 : piece;
+  job.c0 = job.split * a.chunk;
+  job.c1 = min(job.c0 + a.chunk, __builtin_amdgcn_readlane(L, lseq));
   return true;
 }
 
-// The plan's own decomposition: every sequence in nsplit splits of chunk keys.
+// The same decomposition in grid order.
 template <int KH>
 __device__ __forceinline__ bool static_job(const VerifyArgs& a, VerifyJob& job) {
   constexpr int kRows = 256 / KH;
@@ -335,10 +301,8 @@ __device__ __forceinline__ bool static_job(const VerifyArgs& a, VerifyJob& job) 
   job.T = min(max(T, 0), a.T_max);
   const int L = min(max(len, 0), a.L_stride);
   if (job.rg * kRows >= job.T * a.G) return false;
-  job.parts = a.nsplit;
   job.c0 = job.split * a.chunk;
   job.c1 = min(job.c0 + a.chunk, L);
-  job.last = job.split == a.nsplit - 1;
   return true;
 }
 
@@ -358,7 +322,7 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int b = job.b, g = job.g, T = job.T;
   const int c0 = job.c0, c1 = job.c1;
-  const bool do_tree = job.last != 0;
+  const bool do_tree = job.split == a.nsplit - 1;
   const int bg = b * a.Hkv + g;
   const int G = a.G;
   const int rows = T * G;
@@ -784,7 +748,7 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
     const int qr = qrow[nb];
     if (qr >= rows) continue;
     const int u = qu[nb], h = qh[nb];
-    if (job.parts == 1) {
+    if (a.nsplit == 1) {
       const float inv = 1.f / l_tot[nb];
       uint16_t* op = a.out + (((size_t)b * a.T_max + u) * a.Hq + h) * kD;
 #pragma unroll
@@ -799,7 +763,7 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
         }
       if (half == 0 && a.lse) a.lse[((size_t)b * a.Hq + h) * a.T_max + u] = (m_run[nb] + log2f(l_tot[nb])) * kLn2;
     } else {
-      const size_t slot = ((size_t)bg * a.cap + job.split) * a.rows_max + qr;
+      const size_t slot = ((size_t)bg * a.nsplit + job.split) * a.rows_max + qr;
       const float inv = l_tot[nb] > 0.f ? 1.f / l_tot[nb] : 0.f;
       uint16_t* wp = a.ws_o + slot * kD;
 #pragma unroll
@@ -817,8 +781,8 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
   }
 }
 
-// SHARED: one wave shares out the batch for its workgroup; otherwise every
-// wave finds its job in the plan's static decomposition.
+// SHARED: one wave finds the workgroup's job in the order of the whole batch;
+// otherwise every wave finds it from the block index.
 template <int KH, bool SHARED>
 __global__ __launch_bounds__(8 * kWave, 1) void tree_verify_kernel(const VerifyArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[kStages * 2 * kTileBytes];
@@ -835,7 +799,7 @@ __global__ __launch_bounds__(8 * kWave, 1) void tree_verify_kernel(const VerifyA
     __shared__ VerifyJob s_job;
     if (threadIdx.x < kWave) {
       job.b = -1;
-      find_job<KH>(a, blockIdx.y * kPlanSeqs, job);
+      find_job<KH>(a, blockIdx.y * a.plan_seqs, job);
       if (threadIdx.x == 0) s_job = job;
     }
     __syncthreads();
@@ -843,8 +807,7 @@ __global__ __launch_bounds__(8 * kWave, 1) void tree_verify_kernel(const VerifyA
     job.b = uni(s_job.b);
     if (job.b < 0) return;
     job.g = uni(s_job.g), job.T = uni(s_job.T), job.rg = uni(s_job.rg);
-    job.c0 = uni(s_job.c0), job.c1 = uni(s_job.c1), job.last = uni(s_job.last);
-    job.parts = uni(s_job.parts), job.split = uni(s_job.split);
+    job.c0 = uni(s_job.c0), job.c1 = uni(s_job.c1), job.split = uni(s_job.split);
   }
   verify_rows<KH>(a, smem, s_mask, job);
 }
@@ -860,46 +823,46 @@ __global__ __launch_bounds__(kCombineRows * 16) void verify_combine_kernel(const
   const int dim = (threadIdx.x & 15) * 8;
   const int b = bg / a.Hkv;
   const int T = min(max(a.node_count[b], 0), a.T_max);
-  const int parts = SHARED ? min(a.ws_parts[b], a.cap) : a.nsplit;   // written for every sequence with a node
-  const size_t row0 = (size_t)bg * a.cap * a.rows_max + qr;   // split 0 of this row
+  // A shared batch has no workgroup for a split without a key or the tree.
+  const int keyed = SHARED ? splits_with_keys(a, min(max(a.lens[b], 0), a.L_stride)) : a.nsplit;
+  const size_t row0 = (size_t)bg * a.nsplit * a.rows_max + qr;   // split 0 of this row
   // One pass over the splits in index order, four at a time.  The maxima and
-  // partials of a group are loaded together, those of the first group (up to
-  // the plan's splits) with node_count and the split count rather than after
-  // them (every slot is in bounds), so a call with up to four splits costs
-  // one memory round trip; the running max moves online.  Split s carries
-  // O_s/l_s with weight l_s 2^(m_s - M).
+  // partials of a group are loaded together, and with node_count and lens
+  // rather than after them (every slot is in bounds; rows past the tree are
+  // dropped at the end), so a call with up to four splits costs one memory
+  // round trip; the running max moves online.  Split s carries O_s/l_s with
+  // weight l_s 2^(m_s - M).  The products that are fused into an addition are
+  // written out, so that they stay the same in every build of the kernel.
   float M = -INFINITY, den = 0.f;
   float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const int first = SHARED ? min(a.nsplit, 4) : 4;
-  for (int s0 = 0, width = first; s0 < (SHARED ? max(parts, 1) : a.nsplit); s0 += width, width = 4) {
+  for (int s0 = 0; s0 < a.nsplit; s0 += 4) {
     float2 ml[4];
     uint4 v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const bool in = SHARED ? j < width && (s0 == 0 || s0 + j < parts) : s0 + j < a.nsplit;
+      const bool in = s0 + j < a.nsplit;
       const size_t slot = row0 + (size_t)(s0 + j) * a.rows_max;
       ml[j] = in ? a.ws_ml[slot] : make_float2(-INFINITY, 0.f);
       v[j] = in ? *reinterpret_cast<const uint4*>(a.ws_o + slot * kD + dim) : make_uint4(0u, 0u, 0u, 0u);
     }
-    if (SHARED && (parts <= 1 || qr >= T * a.G)) return;   // written by the attention kernel, or past the tree
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if ((!SHARED || s0 + j < parts) && ml[j].y > 0.f) {
+      if ((!SHARED || s0 + j < keyed || s0 + j == a.nsplit - 1) && ml[j].y > 0.f) {
         const float m_new = fmaxf(M, ml[j].x);
         const float c = exp2f(M - m_new);   // 0 while nothing has been merged
         const float w = ml[j].y * exp2f(ml[j].x - m_new);
         const uint32_t wv[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          num[2 * e] = num[2 * e] * c + w * bf16_lo(wv[e]);
-          num[2 * e + 1] = num[2 * e + 1] * c + w * bf16_hi(wv[e]);
+          num[2 * e] = fmaf(num[2 * e], c, w * bf16_lo(wv[e]));
+          num[2 * e + 1] = fmaf(w, bf16_hi(wv[e]), num[2 * e + 1] * c);
         }
-        den = den * c + w;
+        den = fmaf(den, c, w);
         M = m_new;
       }
     }
   }
-  if (!SHARED && qr >= T * a.G) return;
+  if (qr >= T * a.G) return;
   const int g = bg - b * a.Hkv;
   const int u = qr / a.G;
   const int h = g * a.G + (qr - u * a.G);
@@ -973,24 +936,15 @@ VerifyPlan plan_verify(int B, int L_stride, int T_max, int Hq, int Hkv) {
 }
 
 namespace {
-// Sharing out costs a workgroup and the combine kernel about 1 us each, so it
-// is taken where pieces are long (a split of at least 16 tiles) or where
-// unsplit workgroups take several rounds, whose order then counts.
 inline bool shares_batch(const VerifyPlan& p, int B, int Hkv) {
-  if (B == 1) return false;
-  return p.nsplit > 1 ? p.chunk >= 16 * kKeyTile : (long)B * Hkv * p.rowgroups > kCUs;
-}
-// A sequence may take up to twice the plan's splits where others take fewer.
-inline int split_cap(const VerifyPlan& p, int B, int Hkv) {
-  return shares_batch(p, B, Hkv) && p.nsplit > 1 ? std::min(2 * p.nsplit, 64) : p.nsplit;
+  return B > 1 && (long)B * Hkv * p.rowgroups * p.nsplit > kCUs;
 }
 }  // namespace
 
-// The partials of every sequence's splits, then the split counts.
 size_t verify_ws_bytes(const VerifyPlan& p, int B, int Hkv) {
   if (p.nsplit <= 1) return 0;
-  const size_t slots = (size_t)B * split_cap(p, B, Hkv) * Hkv * p.rows_max;
-  return slots * (kD * sizeof(uint16_t) + sizeof(float2)) + (size_t)B * sizeof(int);
+  const size_t slots = (size_t)B * Hkv * p.nsplit * p.rows_max;
+  return slots * kD * sizeof(uint16_t) + slots * sizeof(float2);
 }
 
 hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* v_ctx,
@@ -1020,25 +974,20 @@ hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, con
   // 16.6 / 17.0, but 4 x 4096 22.8 / 22.1.  So small caches load plainly.
   constexpr size_t kPlainBytes = (size_t)64 << 20;
   a.stream = (size_t)B * L_stride * Hkv * 2 * kRowBytes >= kPlainBytes;
-  a.cap = split_cap(p, B, Hkv);
-  const size_t slots = (size_t)B * a.cap * Hkv * p.rows_max;
+  const size_t slots = (size_t)B * Hkv * p.nsplit * p.rows_max;
   a.ws_o = static_cast<uint16_t*>(ws);
   a.ws_ml = ws ? reinterpret_cast<float2*>(static_cast<char*>(ws) + slots * kD * sizeof(uint16_t)) : nullptr;
-  a.ws_parts = ws ? reinterpret_cast<int*>(a.ws_ml + slots) : nullptr;
 
-  // Slots per XCD for the sequences of one plan (64 at most): unsplit they
-  // take one workgroup per (row group, kv head), split at most rounds * kCUs
-  // in all.  Where the units of a sequence go round-robin over groups of
-  // XCDs, a group takes at most one unit of every sequence more than its
-  // even share.
-  const int n = std::min(B, kPlanSeqs);
-  const int heads = Hkv / a.head_cols;
-  int wgs = n * p.rowgroups * Hkv;
-  a.max_wgs = (wgs * p.nsplit + kCUs - 1) / kCUs * kCUs;
-  if (p.nsplit > 1) wgs = std::max(wgs, a.max_wgs);
-  const int slots_xcd = shared ? (wgs + 7) / 8 + (a.head_cols < 8 ? n * p.rowgroups * heads : 0)
+  // Batches beyond one plan's lanes are planned in equal parts.  Slots per XCD
+  // for the sequences of one plan: their units, at most nsplit per sequence,
+  // go round-robin over groups of head_cols XCDs, and one takes at most
+  // rowgroups slots for each of its heads on an XCD.
+  const int plans = shared ? (B + kPlanSeqs - 1) / kPlanSeqs : 1;
+  a.plan_seqs = (B + plans - 1) / plans;
+  const int groups = 8 / a.head_cols;
+  const int slots_xcd = shared ? (a.plan_seqs * p.nsplit + groups - 1) / groups * p.rowgroups * (Hkv / a.head_cols)
                                : (B * Hkv * p.nsplit + 7) / 8 * p.rowgroups;
-  const dim3 grid(slots_xcd * 8, shared ? (B + kPlanSeqs - 1) / kPlanSeqs : 1);
+  const dim3 grid(slots_xcd * 8, plans);
   const dim3 block(8 * kWave);
   if (p.kh == 2 && shared)
     hipLaunchKernelGGL((tree_verify_kernel<2, true>), grid, block, 0, stream, a);

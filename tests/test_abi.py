@@ -256,6 +256,24 @@ def test_binding_refuses_cpu_tensors():
         binding.lexical_match(t, torch.zeros(2, dtype=torch.int32), 2)
 
 
+@pytest.mark.parametrize("B,L,d,k,T,Hq,Hkv", [
+    (1, 512, 4096, 4, 36, 32, 32), (1, 4096, 4096, 8, 44, 32, 8), (16, 8192, 4096, 8, 52, 32, 8),
+    (64, 2048, 5120, 8, 136, 40, 8), (8, 32768, 8192, 16, 72, 64, 8), (24, 6007, 3584, 10, 35, 28, 4),
+    (24, 16612, 5120, 8, 35, 40, 8)])
+def test_step_workspace_is_one_partial_per_split(lib, B, L, d, k, T, Hq, Hkv):
+    """The step's workspace at ordinary sizes: the rerank's lists and one
+    partial per split of the plan, which fits the array of the
+    allocation-free step."""
+    plan = binding.verify_plan(B, L, T, Hq, Hkv)
+    rows = B * Hkv * plan["nsplit"] * T * (Hq // Hkv) if plan["nsplit"] > 1 else 0
+    assert lib.adapld_workspace_bytes(4, B, L, 0, 0, T, Hq, Hkv, 128) == rows * (2 * 128 + 8)
+    need = lib.adapld_workspace_bytes(7, B, L, d, k, T, Hq, Hkv, 128)
+    assert need == B * min(L, 1024) * k * 8 + rows * (2 * 128 + 8) <= 64 << 20
+    f = lib.adapld_step_noalloc   # stopped by scale = 0 (or, without a GPU, by the array's lookup), not by its size
+    args = [P] * 3 + [N] + [P] * 5 + [B, L, d, 4, k, 1, T - 1, T, Hq, Hkv, 128, float("nan"), 0, 0.0] + [P] * 15 + [N]
+    assert f(*args) in (INVALID, -5)
+
+
 def test_step_noalloc_validation(lib):
     """The allocation-free step refuses, before any HIP call, sizes whose
     workspace exceeds its device array (host-only checks: no GPU needed)."""

@@ -69,3 +69,13 @@ def test_noalloc_step_two_calls():
     xs = make_inputs(small, lens=np.array([700, 333, 2], np.int32))
     _compare(xs, small, "second (smaller)")
     _compare(xs, small, "third (smaller, rows j-1 against row L-2)", preceding=True)
+
+
+def test_noalloc_step_shared_workgroups():
+    # a split verify whose workgroups take two rounds and are shared out by
+    # length and tree size
+    cfg = small_config(B=6, L=4100, d=64, k=8, n_max=3, seed=303, V=300, Hq=24, Hkv=3, W=8, S=16, forced_every=2)
+    info = adapld.verify_plan(cfg.B, cfg.L, cfg.T_max, cfg.Hq, cfg.Hkv)
+    assert info["nsplit"] > 1 and cfg.B * cfg.Hkv * info["rowgroups"] * info["nsplit"] > 256, info
+    x = make_inputs(cfg, lens=np.array([4100, 2000, 3, 4099, 64, 1408], np.int32))
+    _compare(x, cfg, "shared")
