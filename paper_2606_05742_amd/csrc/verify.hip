@@ -711,6 +711,8 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
     // ring, which no wave reads any more after this barrier; lane i of both
     // waves holds the same query column.  Each state is relative to its own
     // running max: the merged one takes M = max(m0, m1) and weights 2^(m - M).
+    // The fused products are written out: left to the compiler, another build
+    // of the kernel fused the other one and gave other bits.
     static_assert(NB == 1, "one row block per wave");
     float4* xo = reinterpret_cast<float4*>(smem);                        // [kBlocks][16][64]
     float2* xml = reinterpret_cast<float2*>(smem + kBlocks * 16 * 64 * 16);   // [kBlocks][64]
@@ -735,12 +737,12 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
         const float4 v = xo[(wrow * 16 + db * 4 + r4) * 64 + lane];
-        o[0][db][4 * r4 + 0] = a0 * o[0][db][4 * r4 + 0] + a1 * v.x;
-        o[0][db][4 * r4 + 1] = a0 * o[0][db][4 * r4 + 1] + a1 * v.y;
-        o[0][db][4 * r4 + 2] = a0 * o[0][db][4 * r4 + 2] + a1 * v.z;
-        o[0][db][4 * r4 + 3] = a0 * o[0][db][4 * r4 + 3] + a1 * v.w;
+        o[0][db][4 * r4 + 0] = fmaf(a1, v.x, a0 * o[0][db][4 * r4 + 0]);
+        o[0][db][4 * r4 + 1] = fmaf(a1, v.y, a0 * o[0][db][4 * r4 + 1]);
+        o[0][db][4 * r4 + 2] = fmaf(a1, v.z, a0 * o[0][db][4 * r4 + 2]);
+        o[0][db][4 * r4 + 3] = fmaf(a1, v.w, a0 * o[0][db][4 * r4 + 3]);
       }
-    l_tot[0] = a0 * l_tot[0] + a1 * ml.y;
+    l_tot[0] = fmaf(a0, l_tot[0], a1 * ml.y);
     m_run[0] = M;
   }
 #pragma unroll
