@@ -48,7 +48,6 @@
 // output's own) with the running max and sum in fp32; a combine kernel merges
 // them with log-sum-exp weights.
 #include <algorithm>
-#include <numeric>
 #include <type_traits>
 
 #include "adapld_internal.h"
@@ -92,7 +91,6 @@ struct VerifyArgs {
   int chunk, rowgroups;   // context keys per split, row groups of a full tree
   int plan_seqs;   // sequences that one plan orders
   int stream;      // nonzero: tiles that one workgroup reads are loaded with the non-temporal hint
-  int head_cols;   // XCDs that the heads of one (sequence, split) unit spread over: gcd(Hkv, 8)
   float scale_log2;
   uint16_t* out;
   float* lse;
@@ -253,14 +251,10 @@ __device__ __forceinline__ bool find_job(const VerifyArgs& a, int base, VerifyJo
   const int rs = packed >> 16;
   const int p1 = wave_incl_scan_i32(ks);   // units up to and including this sequence
   const int p0 = p1 - ks;
-  // Units go round-robin over the XCD groups of head_cols XCDs each.
+  // (unit, kv head) pairs go round-robin over the XCDs.
   const int xcd = blockIdx.x & 7;
-  const int cols_log2 = __builtin_ctz(a.head_cols);
-  const int sub = xcd >> cols_log2;
-  const int groups = 8 >> cols_log2;
-  const int heads = a.Hkv >> cols_log2;    // heads of a unit on one XCD
-  const int mine = ((p1 + groups - 1 - sub) >> (3 - cols_log2)) - ((p0 + groups - 1 - sub) >> (3 - cols_log2));
-  const int slots = mine * rs * heads;
+  const int mine = ((p1 * a.Hkv + 7 - xcd) >> 3) - ((p0 * a.Hkv + 7 - xcd) >> 3);
+  const int slots = mine * rs;
   const int incl = wave_incl_scan_i32(slots);
   const int slot = blockIdx.x >> 3;
   const uint64_t at = __ballot(incl > slot);
@@ -268,13 +262,13 @@ __device__ __forceinline__ bool find_job(const VerifyArgs& a, int base, VerifyJo
   const int li = __builtin_ctzll(at);
   const int ri = __builtin_amdgcn_readlane(rs, li);
   const int rem = slot - __builtin_amdgcn_readlane(incl - slots, li);
-  const int u0 = __builtin_amdgcn_readlane(p0, li);
+  const int pair0 = __builtin_amdgcn_readlane(p0, li) * a.Hkv;
   const int lseq = __builtin_amdgcn_readlane(src, li);
-  const int kv = div_small(rem, ri);
-  job.rg = rem - kv * ri;
-  const int ul = div_small(kv, heads);
-  job.g = (xcd & (a.head_cols - 1)) + a.head_cols * (kv - ul * heads);
-  const int piece = ((sub - u0) & (groups - 1)) + groups * ul;
+  const int at_xcd = div_small(rem, ri);
+  job.rg = rem - at_xcd * ri;
+  const int pair = ((xcd - pair0) & 7) + 8 * at_xcd;   // of the sequence
+  const int piece = div_small(pair, a.Hkv);
+  job.g = pair - piece * a.Hkv;
   job.b = base + lseq;
   job.T = __builtin_amdgcn_readlane(T, lseq);
   // the pieces are the splits with a key, then the last split
@@ -960,7 +954,6 @@ hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, con
   a.lens = lens; a.node_count = node_count; a.tree_mask = tree_mask;
   a.B = B; a.L_stride = L_stride; a.T_max = T_max; a.Hq = Hq; a.Hkv = Hkv; a.G = p.G;
   a.rows_max = p.rows_max; a.nw = (T_max + 63) / 64; a.nsplit = p.nsplit;
-  a.head_cols = std::gcd(Hkv, 8);
   a.scale_log2 = scale * kLog2e;
   a.out = out; a.lse = lse;
   const bool shared = shares_batch(p, B, Hkv);
@@ -981,14 +974,11 @@ hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, con
   a.ws_ml = ws ? reinterpret_cast<float2*>(static_cast<char*>(ws) + slots * kD * sizeof(uint16_t)) : nullptr;
 
   // Batches beyond one plan's lanes are planned in equal parts.  Slots per XCD
-  // for the sequences of one plan: their units, at most nsplit per sequence,
-  // go round-robin over groups of head_cols XCDs, and one takes at most
-  // rowgroups slots for each of its heads on an XCD.
+  // of one plan: its (sequence, piece, kv head) triples go round-robin over the
+  // XCDs and take at most rowgroups slots each.
   const int plans = shared ? (B + kPlanSeqs - 1) / kPlanSeqs : 1;
   a.plan_seqs = (B + plans - 1) / plans;
-  const int groups = 8 / a.head_cols;
-  const int slots_xcd = shared ? (a.plan_seqs * p.nsplit + groups - 1) / groups * p.rowgroups * (Hkv / a.head_cols)
-                               : (B * Hkv * p.nsplit + 7) / 8 * p.rowgroups;
+  const int slots_xcd = (a.plan_seqs * Hkv * p.nsplit + 7) / 8 * p.rowgroups;
   const dim3 grid(slots_xcd * 8, plans);
   const dim3 block(8 * kWave);
   if (p.kh == 2 && shared)
