@@ -777,8 +777,10 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
   }
 }
 
-// SHARED: one wave finds the workgroup's job in the order of the whole batch;
-// otherwise every wave finds it from the block index.
+// SHARED: the workgroup's job comes from the order of the whole batch, which
+// every wave works out (a barrier and a trip through LDS cost more than the
+// repeated work: 65 sequences of up to 300 keys, 40 heads over 8, 67.1 -> 66.3
+// us a call in two rounds); otherwise from the block index.
 template <int KH, bool SHARED>
 __global__ __launch_bounds__(8 * kWave, 1) void tree_verify_kernel(const VerifyArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[kStages * 2 * kTileBytes];
@@ -792,18 +794,7 @@ __global__ __launch_bounds__(8 * kWave, 1) void tree_verify_kernel(const VerifyA
   if constexpr (!SHARED) {
     if (!static_job<KH>(a, job)) return;
   } else {
-    __shared__ VerifyJob s_job;
-    if (threadIdx.x < kWave) {
-      job.b = -1;
-      find_job<KH>(a, blockIdx.y * a.plan_seqs, job);
-      if (threadIdx.x == 0) s_job = job;
-    }
-    __syncthreads();
-    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
-    job.b = uni(s_job.b);
-    if (job.b < 0) return;
-    job.g = uni(s_job.g), job.T = uni(s_job.T), job.rg = uni(s_job.rg);
-    job.c0 = uni(s_job.c0), job.c1 = uni(s_job.c1), job.split = uni(s_job.split);
+    if (!find_job<KH>(a, blockIdx.y * a.plan_seqs, job)) return;
   }
   verify_rows<KH>(a, smem, s_mask, job);
 }
@@ -932,8 +923,18 @@ VerifyPlan plan_verify(int B, int L_stride, int T_max, int Hq, int Hkv) {
 }
 
 namespace {
+// In one round of workgroups their order is nothing.  In several, a call gains
+// where its sequences differ and pays about 0.5 us a round for the planning:
+// us a call in grid order / ordered, equal full sequences, then lengths of a
+// third to all of the capacity, then equal lengths and trees of a fifth to all
+// of the nodes: 40 x 1000 keys, 32 heads over 8, 60 nodes 82.3 / 82.9, 49.1 /
+// 42.1, 63.3 / 52.8; 64 x 2048, 40 over 8, 136 nodes 459 / 462, 222 / 207, 388
+// / 356; 12 x 8000, 64 over 8, 52 nodes 213 / 214, 154 / 123, 165 / 172; pair
+// shape, 8 x 32768, 64 over 8, 72 nodes 705 / 708, 499 / 387, 453 / 445.  The
+// short workgroups of the pair shape don't repay it: 128 x 512 keys, 32 over
+// 32, 30 nodes 244.5 / 253.4, 200.4 / 216.6, 243.3 / 249.0.
 inline bool shares_batch(const VerifyPlan& p, int B, int Hkv) {
-  return B > 1 && (long)B * Hkv * p.rowgroups * p.nsplit > kCUs;
+  return B > 1 && (long)B * Hkv * p.rowgroups * p.nsplit > kCUs && (p.kh == 1 || p.chunk >= 16 * kKeyTile);
 }
 }  // namespace
 
