@@ -90,7 +90,6 @@ struct VerifyArgs {
   int nsplit;      // splits per sequence (1: no sequence is split)
   int chunk, rowgroups;   // context keys per split, row groups of a full tree
   int plan_seqs;   // sequences that one plan orders
-  int stream;      // nonzero: tiles that one workgroup reads are loaded with the non-temporal hint
   float scale_log2;
   uint16_t* out;
   float* lse;
@@ -150,16 +149,15 @@ __device__ __forceinline__ void dma16_s_stream(const void* gbase, uint32_t voff,
 
 // The same share of a tile whose 64 keys are all below kend (no clamping):
 // the row addresses are a scalar base plus lane offsets fixed per wave.
-template <int WAVES>
+template <int WAVES, bool STREAM>
 __device__ __forceinline__ void issue_tile_full(const uint16_t* kb, const uint16_t* vb, int k0, uint32_t lk,
-                                                uint32_t lv, int wave, const uint32_t (&voff)[64 / WAVES / 4],
-                                                bool stream) {
+                                                uint32_t lv, int wave, const uint32_t (&voff)[64 / WAVES / 4]) {
   constexpr int kRowsPerWave = kKeyTile / WAVES;
 #pragma unroll
   for (int i = 0; i < kRowsPerWave / 4; ++i) {
     const int row0 = kRowsPerWave * wave + 4 * i;
     const size_t key0 = (size_t)(k0 + row0);
-    if (stream) {   // wave-uniform
+    if constexpr (STREAM) {
       dma16_s_stream(kb + key0 * kD, voff[i], lk + row0 * kRowBytes);
       dma16_s_stream(vb + key0 * kD, voff[i], lv + row0 * kRowBytes);
     } else {
@@ -302,7 +300,7 @@ __device__ __forceinline__ bool static_job(const VerifyArgs& a, VerifyJob& job) 
 
 // One row group's share of one split: 32 * kBlocks stacked rows of (b, g)
 // against the keys [c0, c1) and, in the last split, the tree's.
-template <int KH>
+template <int KH, bool STREAM>
 __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, uint64_t* s_mask,
                                             const VerifyJob& job) {
   constexpr int NB = 1, WAVES = 8;
@@ -321,7 +319,6 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
   const int G = a.G;
   const int rows = T * G;
   const int row_base = job.rg * (kBlocks * 32);
-  const bool stream = a.stream && rows <= kBlocks * 32;   // no other row group reads these tiles
   // Row block of this wave, and (KH = 2) the half of every tile it takes.
   const int wrow = KH == 2 ? wave % kBlocks : wave;
   const int kh = KH == 2 ? wave / kBlocks : 0;
@@ -392,7 +389,7 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
     if (t < n_ctx) {
       const int k0 = c0 + t * kKeyTile;
       if (k0 + kKeyTile <= c1)
-        issue_tile_full<WAVES>(kc, vc, k0, lk, lv, wave, voff, stream);
+        issue_tile_full<WAVES, STREAM>(kc, vc, k0, lk, lv, wave, voff);
       else
         issue_tile<WAVES>(kc, vc, kD, k0, c1, lk, lv, wave, lane);
     } else {
@@ -781,7 +778,7 @@ __device__ __forceinline__ void verify_rows(const VerifyArgs& a, uint8_t* smem, 
 // every wave works out (a barrier and a trip through LDS cost more than the
 // repeated work: 65 sequences of up to 300 keys, 40 heads over 8, 67.1 -> 66.3
 // us a call in two rounds); otherwise from the block index.
-template <int KH, bool SHARED>
+template <int KH, bool SHARED, bool STREAM>
 __global__ __launch_bounds__(8 * kWave, 1) void tree_verify_kernel(const VerifyArgs a) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[kStages * 2 * kTileBytes];
   __shared__ uint64_t s_mask[ADAPLD_MAX_TREE_NODES * kMaskWords];
@@ -796,7 +793,7 @@ __global__ __launch_bounds__(8 * kWave, 1) void tree_verify_kernel(const VerifyA
   } else {
     if (!find_job<KH>(a, blockIdx.y * a.plan_seqs, job)) return;
   }
-  verify_rows<KH>(a, smem, s_mask, job);
+  verify_rows<KH, STREAM>(a, smem, s_mask, job);
 }
 
 // Merge the splits: 8 stacked rows per workgroup, 16 threads x 8 dims (one
@@ -969,7 +966,7 @@ hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, con
   // and plain loads win where the call is small: 3 x 3000 19.9 / 21.5, 1 x 2000
   // 16.6 / 17.0, but 4 x 4096 22.8 / 22.1.  So small caches load plainly.
   constexpr size_t kPlainBytes = (size_t)64 << 20;
-  a.stream = (size_t)B * L_stride * Hkv * 2 * kRowBytes >= kPlainBytes;
+  const bool stream_kv = p.rowgroups == 1 && (size_t)B * L_stride * Hkv * 2 * kRowBytes >= kPlainBytes;
   const size_t slots = (size_t)B * Hkv * p.nsplit * p.rows_max;
   a.ws_o = static_cast<uint16_t*>(ws);
   a.ws_ml = ws ? reinterpret_cast<float2*>(static_cast<char*>(ws) + slots * kD * sizeof(uint16_t)) : nullptr;
@@ -982,14 +979,18 @@ hipError_t launch_tree_verify_attn(const uint16_t* q, const uint16_t* k_ctx, con
   const int slots_xcd = (a.plan_seqs * Hkv * p.nsplit + 7) / 8 * p.rowgroups;
   const dim3 grid(slots_xcd * 8, plans);
   const dim3 block(8 * kWave);
-  if (p.kh == 2 && shared)
-    hipLaunchKernelGGL((tree_verify_kernel<2, true>), grid, block, 0, stream, a);
-  else if (p.kh == 2)
-    hipLaunchKernelGGL((tree_verify_kernel<2, false>), grid, block, 0, stream, a);
-  else if (shared)
-    hipLaunchKernelGGL((tree_verify_kernel<1, true>), grid, block, 0, stream, a);
-  else
-    hipLaunchKernelGGL((tree_verify_kernel<1, false>), grid, block, 0, stream, a);
+  auto launch = [&](auto kh, auto sh, auto st) {
+    hipLaunchKernelGGL((tree_verify_kernel<decltype(kh)::value, decltype(sh)::value, decltype(st)::value>), grid, block, 0,
+                       stream, a);
+  };
+  auto launch_kh = [&](auto kh) {
+    if (shared && stream_kv) launch(kh, std::true_type{}, std::true_type{});
+    else if (shared) launch(kh, std::true_type{}, std::false_type{});
+    else if (stream_kv) launch(kh, std::false_type{}, std::true_type{});
+    else launch(kh, std::false_type{}, std::false_type{});
+  };
+  if (p.kh == 2) launch_kh(std::integral_constant<int, 2>{});
+  else launch_kh(std::integral_constant<int, 1>{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.nsplit == 1) return e;
   const dim3 cgrid((p.rows_max + kCombineRows - 1) / kCombineRows, B * Hkv);
