@@ -11,8 +11,8 @@
 // tile each (KH = 2): then every tile is read from LDS once per row block,
 // not once per wave, and the pair merges its two softmax states through LDS
 // at the end, so a workgroup covers twice the keys without a second split.
-// The grid is one-dimensional and XCD-aware (see the block index decode in
-// the kernel).
+// The grid is XCD-aware (see the work assignment below); batches that are
+// ordered by length have a second dimension, one row per plan.
 //
 // Memory pipeline.  K and V tiles of 64 keys stream through a 4-stage LDS ring
 // with direct-to-LDS loads (global_load_lds_dwordx4): no VGPR staging, and up
@@ -195,6 +195,7 @@ __device__ __forceinline__ void wait_tile_and_sync(int later) {
 // consecutive slots on one XCD (workgroups go round-robin over the 8 XCDs), so
 // the second reader of a K/V tile finds it in that XCD's L2.
 constexpr int kPlanSeqs = kWave;       // most sequences ordered together: one per lane
+constexpr int kPlanRowgroups = 0x7fff; // most row groups of one sequence in an order
 constexpr int kCostWide = 16;          // cost of one tile of a row group of 5 to 8 blocks: two waves' rows per SIMD
 constexpr int kCostNarrow = 12;        // of one of up to 4 blocks
 constexpr int kCUs = 256;
@@ -931,7 +932,8 @@ namespace {
 // short workgroups of the pair shape don't repay it: 128 x 512 keys, 32 over
 // 32, 30 nodes 244.5 / 253.4, 200.4 / 216.6, 243.3 / 249.0.
 inline bool shares_batch(const VerifyPlan& p, int B, int Hkv) {
-  return B > 1 && (long)B * Hkv * p.rowgroups * p.nsplit > kCUs && (p.kh == 1 || p.chunk >= 16 * kKeyTile);
+  return B > 1 && p.rowgroups <= kPlanRowgroups && (long)B * Hkv * p.rowgroups * p.nsplit > kCUs &&
+         (p.kh == 1 || p.chunk >= 16 * kKeyTile);
 }
 }  // namespace
 

@@ -90,3 +90,22 @@ def test_neighbours_leave_a_sequence_alone(B, L, T, HQ, HKV):
         for b, now, was in zip(at, got, seen or got):
             assert torch.equal(now[0], was[0]) and torch.equal(now[1], was[1]), (mates, b)
         seen = got
+
+
+def test_most_row_groups():
+    """More row groups than the 15 bits that an order keeps of them."""
+    B, L, T, HQ = 2, 1, 256, 32768
+    p = adapld.verify_plan(B, L, T, HQ, 1)
+    assert p["rowgroups"] > 32767, p
+    dev = dict(dtype=torch.bfloat16, device="cuda")
+    q, kc, kt = torch.zeros((B, T, HQ, 128), **dev), torch.zeros((B, 1, L, 128), **dev), torch.zeros((B, T, 1, 128), **dev)
+    vt = torch.randn((B, T, 1, 128), device="cuda").bfloat16()
+    bits = torch.zeros((T, T // 64, 64), dtype=torch.bool)
+    u = torch.arange(T)
+    bits[u, u // 64, u % 64] = True
+    words = np.packbits(bits.numpy(), axis=2, bitorder="little").view(np.int64).reshape(1, T, T // 64)
+    mask = torch.from_numpy(np.repeat(words, B, 0)).cuda()
+    i32 = lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")  # noqa: E731
+    out, _ = adapld.tree_verify_attn(q, kc, kc, kt, vt, i32(0, 0), i32(T, 3), mask, with_lse=False)
+    assert torch.equal(out[0], vt[0].expand(T, HQ, 128))
+    assert torch.equal(out[1, :3], vt[1, :3].expand(3, HQ, 128))
