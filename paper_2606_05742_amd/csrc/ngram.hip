@@ -61,7 +61,7 @@ struct NgHeader {
   int magic;         // kNgMagic once a build has initialised the level
 };
 
-constexpr int kNgMagic = 0x6e677231;
+constexpr int kNgMagic = 0x6e677232;   // of this hash and probing; an index laid out otherwise counts as never built
 constexpr size_t kNgRegion = 8192;   // slots per region (a smaller table is one region)
 
 struct NgLevel {

@@ -197,3 +197,21 @@ def test_index_lookup_beside_insertions(m, n_max):
         tok_d.copy_(torch.from_numpy(tok))
         lens_d.copy_(torch.from_numpy(lens))
         check(idx, tok, lens, tok_d, lens_d, n_max, f"m={m} step {step}", fused=True)
+
+
+def test_index_of_another_layout_is_not_read():
+    """A level whose header names another layout (an index that was saved by a
+    library with another hash) is stale to a match and rebuilt by an append."""
+    L, n_max = 900, 3
+    tok = np.random.default_rng(5).integers(0, 30, (1, L)).astype(np.int32)
+    lens = np.array([L], np.int32)
+    tok_d, lens_d = torch.from_numpy(tok).cuda(), torch.from_numpy(lens).cuda()
+    idx = adapld.NgramIndex(1, L, n_max).build(tok_d, lens_d)
+    check(idx, tok, lens, tok_d, lens_d, n_max, "build")
+    level = idx.buf.numel() // n_max
+    header = 2048 * 16 + (12 * L + 16) * 4          # behind the table and the pool
+    words = idx.buf[level + header:level + header + 16].view(torch.int32)
+    assert int(words[1]) == L
+    words[3] = 0x6e677231                            # the layout whose tables were placed by a 64-bit hash
+    check(idx, tok, lens, tok_d, lens_d, n_max, "older layout", stale=(0,))
+    check(idx, tok, lens, tok_d, lens_d, n_max, "append", fused=True)
