@@ -14,9 +14,10 @@
 //
 // build kernel: one workgroup per region of a level's table (see its comment).
 //
-// update kernel (appends with more levels than one workgroup has waves): one
-// workgroup per (level, sequence).  The positions that became candidates since
-// the last update (all of them when the context shrank) are inserted in
+// update kernel (appends with more levels than one workgroup has waves, and
+// builds of levels with an overfull region): one workgroup per (level,
+// sequence).  The positions that became candidates since the last update (all
+// of them when the level starts from scratch) are inserted in
 // batches of 256 in ascending order: each batch is sorted by n-gram hash,
 // equal n-grams form contiguous groups (checked token by token; a hash
 // collision inside a batch falls back to inserting that batch one position at
@@ -117,7 +118,8 @@ __device__ __forceinline__ uint64_t ng_hash(const int32_t* M, int j, int n) {
 }
 
 __device__ __forceinline__ bool ng_equal(const int32_t* M, int j0, int j1, int n) {
-  for (int i0 = 0; i0 < n; i0 += 4) {
+  int differ = 0;
+  for (int i0 = 0; i0 < n && differ == 0; i0 += 4) {
     int x[4], y[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -125,34 +127,41 @@ __device__ __forceinline__ bool ng_equal(const int32_t* M, int j0, int j1, int n
       x[i] = M[j0 - k];
       y[i] = M[j1 - k];
     }
-    if (x[0] != y[0] || x[1] != y[1] || x[2] != y[2] || x[3] != y[3]) return false;
+    differ = (x[0] ^ y[0]) | (x[1] ^ y[1]) | (x[2] ^ y[2]) | (x[3] ^ y[3]);
   }
-  return true;
+  return differ == 0;
 }
 
 // The slot of the n-gram ending at j (creating it when `insert`), or -1 when
 // it is absent.  Probing is linear and wraps inside the slot's region of
-// kNgRegion slots, so that a build can give each region to one workgroup.
-// The table is at most half full, so an empty slot ends every probe; the loop
-// is bounded by the region's size all the same.
-__device__ int ng_probe(const NgLevel& lv, const int32_t* M, int j, int n, uint64_t h, bool insert, bool& created) {
-  created = false;
-  size_t s = h & lv.mask;
+// kNgRegion slots, so that a build can give each region to one workgroup; a
+// region that is full goes on in the next one.  The table is at most half
+// full, so an empty slot ends every probe; the loop is bounded by the table's
+// size all the same.
+//
+// The result is one variable that is set on every path: with a return at each
+// end of the search, the inlined result was undefined in the loop, and one
+// build read an unset register for the lanes that had found their n-gram.
+__device__ __forceinline__ int ng_probe(const NgLevel& lv, const int32_t* M, int j, int n, uint64_t h, bool insert,
+                                        bool& created) {
   const size_t rm = lv.mask < kNgRegion - 1 ? lv.mask : kNgRegion - 1;
-  for (size_t step = 0; step <= rm; ++step, s = (s & ~rm) | ((s + 1) & rm)) {
+  size_t s = h & lv.mask;
+  int at = -1;
+  created = false;
+  for (size_t left = lv.mask + 1; left != 0; --left) {
     int k = __hip_atomic_load(&lv.tab[s].key_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    if (k < 0) {
-      if (!insert) return -1;
-      const int prev = atomicCAS(&lv.tab[s].key_end, -1, j);
-      if (prev == -1) {
-        created = true;
-        return (int)s;
-      }
-      k = prev;
+    if (k < 0 && insert) {
+      k = atomicCAS(&lv.tab[s].key_end, -1, j);
+      created = k < 0;
     }
-    if (ng_equal(M, k, j, n)) return (int)s;
+    if (k < 0 || ng_equal(M, k, j, n)) {   // empty (or claimed just now), or found
+      at = k >= 0 || created ? (int)s : -1;
+      break;
+    }
+    s = (s & ~rm) | ((s + 1) & rm);
+    if (((left - 1) & rm) == 0) s = (s + rm + 1) & lv.mask;   // the region is full
   }
-  return -1;
+  return at;
 }
 
 __device__ __forceinline__ int pow2_at_least(int v) {
@@ -507,7 +516,7 @@ __device__ __forceinline__ void build_group(const int32_t* __restrict__ M, int n
       const int o = atomicCAS(&s.key[at], -1, j);
       if (o == -1 || ng_equal(M, o, j, n)) break;
     }
-    if (step > rm) s.over = 1;   // a full region: the level is marked unusable
+    if (step > rm) s.over = 1;   // more n-grams than the region has slots: the level is built by the update kernel
     s.slot[i] = (uint16_t)at;
   }
 }
@@ -868,6 +877,12 @@ hipError_t launch_ngram_build(const int32_t* tokens, const int32_t* lens, int B,
   const size_t slots = ngram_slots(L_stride);
   const unsigned regions = (unsigned)((slots + kNgRegion - 1) / kNgRegion);
   hipLaunchKernelGGL(ngram_build_kernel, dim3(regions, n_max, B), dim3(kBuildThreads), 0, stream, a);
+  // One region holds every n-gram of its context.  Of several, one can get more
+  // than it has slots (chosen tokens; never seen in text); the update kernel
+  // then builds that level anew, going on in the next region, and finds
+  // nothing to do in the others.
+  if ((e = hipGetLastError()) != hipSuccess || regions == 1) return e;
+  hipLaunchKernelGGL(ngram_update_kernel, dim3(n_max, B), dim3(kNgThreads), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -215,3 +215,77 @@ def test_index_of_another_layout_is_not_read():
     words[3] = 0x6e677231                            # the layout whose tables were placed by a 64-bit hash
     check(idx, tok, lens, tok_d, lens_d, n_max, "older layout", stale=(0,))
     check(idx, tok, lens, tok_d, lens_d, n_max, "append", fused=True)
+
+
+def crowded_tokens(count, slots, region, rng, region_slots=8192):
+    """`count` distinct tokens whose one-token n-gram starts in one region of
+    the table (the index's hash, here in numpy)."""
+    def mul(h, c):
+        return (h.astype(np.uint64) * np.uint64(c) & np.uint64(0xffffffff)).astype(np.uint32)
+    t = np.unique(rng.integers(0, 1 << 31, 2 * count * (slots // region_slots)).astype(np.uint32))
+    h = mul(np.uint32(1) ^ t, 0x9E3779B1)
+    h ^= h >> np.uint32(15)
+    h = mul(h ^ (h >> np.uint32(16)), 0x85EBCA6B)
+    h = mul(h ^ (h >> np.uint32(13)), 0xC2B2AE35)
+    h ^= h >> np.uint32(16)
+    t = t[(h & np.uint32(slots - 1)) // np.uint32(region_slots) == region]
+    assert len(t) >= count
+    return rng.permutation(t)[:count].astype(np.int32)
+
+
+@pytest.mark.parametrize("n_max", [2, 18])
+@pytest.mark.parametrize("built", [True, False])
+def test_index_full_region(built, n_max):
+    """More distinct tokens that start in one region of the table than it has
+    slots: the last region (which wraps to the first) and an inner one, through
+    a build and through an append to an index never built, then appends (18
+    levels take the kernel with one workgroup per level)."""
+    rng = np.random.default_rng(17)
+    L, cap = 17000, 17600
+    slots = 65536
+    tok = rng.integers(0, 1000, (2, cap)).astype(np.int32)
+    crowd = np.stack([crowded_tokens(9000, slots, r, rng) for r in (slots // 8192 - 1, 3)])
+    tok[:, 100:8900] = crowd[:, :8800]
+    lens = np.full(2, L, np.int32)
+    tok[:, L - 1] = crowd[:, 8700]                # the query: one of the crowd, at two more places
+    tok[:, [50, 12000]] = crowd[:, 8700:8701]
+    tok_d, lens_d = torch.from_numpy(tok).cuda(), torch.from_numpy(lens).cuda()
+    idx = adapld.NgramIndex(2, cap, n_max)
+    if built:
+        idx.build(tok_d, lens_d)
+    else:
+        idx.buf.zero_()
+        idx.append(tok_d, lens_d)
+    check(idx, tok, lens, tok_d, lens_d, n_max, "first")
+    for step, fused in enumerate((False, True, True)):
+        lo, hi = int(lens[0]), int(lens[0]) + 70
+        tok[:, lo:hi] = crowd[:, rng.integers(8000, 9000, 70)]   # some of them new
+        lens[:] = hi
+        tok_d.copy_(torch.from_numpy(tok))
+        lens_d.copy_(torch.from_numpy(lens))
+        if not fused:
+            idx.append(tok_d, lens_d)
+        check(idx, tok, lens, tok_d, lens_d, n_max, f"step {step}", fused=fused)
+
+
+@pytest.mark.parametrize("n_max", [17, 20])
+def test_index_one_workgroup_per_level(n_max):
+    """More levels than the append kernel has waves: an index never built, a
+    rollback, several batches of 256 positions in one append, and arrays that
+    move to larger ones."""
+    rng = np.random.default_rng(n_max)
+    B, L, cap = 3, 900, 2600
+    tok = rng.integers(0, 4, (B, cap)).astype(np.int32)
+    tok[1] = 6                                       # one token throughout: every array moves
+    tok[2, 600:640] = tok[2, 860:900]
+    lens = np.array([L, L - 1, L], np.int32)
+    tok_d, lens_d = torch.from_numpy(tok).cuda(), torch.from_numpy(lens).cuda()
+    idx = adapld.NgramIndex(B, cap, n_max)
+    idx.buf.zero_()
+    for step, grow_by in enumerate((0, 700, -500, 257, 1, 900)):
+        lens += grow_by
+        lens_d.copy_(torch.from_numpy(lens))
+        fused = step % 2 == 0
+        if not fused:
+            idx.append(tok_d, lens_d)
+        check(idx, tok, lens, tok_d, lens_d, n_max, f"step {step}", fused=fused)
