@@ -456,11 +456,15 @@ __global__ __launch_bounds__(kNgThreads) void ngram_update_kernel(const NgArgs a
 //
 // What bounds it: the latency of a dozen dependent phases and the writing of
 // the table (16 bytes per slot, at least two slots per position of capacity).
-// Build calls with 4 levels, against one workgroup per level that sorted 256
-// positions at a time: 16 x 8192 tokens 31.9 us (417; 56 for workgroups that
-// claimed slots of a cleared table by global atomics), 8 x 32768 193 (1672),
-// 1 x 131072 337 (6488), 64 x 2048 23.5 (115), 1 x 512 12.3 (25.7).  Every
-// region's workgroup hashes the whole row, which is what the longer rows pay.
+// Build calls against one workgroup per level that sorts 256 positions at a
+// time (the update kernel), us, Zipf tokens over 128 Ki ids, 4 levels: 1 x 512
+// 34 / 12, 16 x 8192 486 / 78, 1 x 131072 7360 / 271, 64 x 32768 2055 / 767;
+// contexts of 2 % of the capacity 16 x 8192 17.8 / 16.3, 64 x 8192 23.3 / 28.7.
+// Threads beyond the context skip the hashes, and a position's probe starts
+// where its listing hash says: 64 levels of 16 x 8192 at 2 % 175 -> 105, full
+// 1231 -> 1075.  Many levels of short rows stay dearer than by level where the
+// contexts are nearly empty or full (57 and 985 there), not between (at 30 %
+// 149 against 280): a near-empty one costs its region's workgroup some 7 us.
 constexpr int kBuildThreads = 1024;
 constexpr int kBuildWaves = kBuildThreads / kWave;
 constexpr int kBuildItems = 4096;            // listed positions
@@ -487,7 +491,7 @@ struct BuildShared {
   uint16_t num[kNgRegion];       // its positions in the current list
   uint16_t first[kNgRegion];     // its first place in grp, then one past its last
   int pos[kBuildItems];          // the list, ascending
-  uint16_t slot[kBuildItems];    // its slots
+  uint16_t slot[kBuildItems];    // where their probes start, then their slots
   uint16_t grp[kBuildItems];     // list indices, group by group
   uint16_t big[kBuildItems / kBuildSmall];
   uint32_t map[kBuildWaves][kBuildItems / 32];
@@ -495,11 +499,12 @@ struct BuildShared {
   int base, nbig, over;
 };
 
-// Finds (or claims) the slots of the listed positions s.pos[0, count).
+// Finds (or claims) the slots of the listed positions s.pos[0, count), from
+// the starts that the listing left there.
 __device__ __forceinline__ void build_group(const int32_t* __restrict__ M, int n, int rm, int count, BuildShared& s) {
   for (int i = threadIdx.x; i < count; i += kBuildThreads) {
     const int j = s.pos[i];
-    int at = (int)(uint32_t)ng_hash(M, j, n) & rm;
+    int at = s.slot[i];
     int step = 0;
     for (; step <= rm; ++step, at = (at + 1) & rm) {
       const int o = atomicCAS(&s.key[at], -1, j);
@@ -617,32 +622,43 @@ __global__ __launch_bounds__(kBuildThreads) void ngram_build_kernel(const NgArgs
     for (int j0 = n - 1; j0 <= L - 2; j0 += kBuildThreads * kBuildRun) {
       const int j = j0 + tid * kBuildRun;
       uint32_t h[kBuildRun];
-#pragma unroll
-      for (int e = 0; e < kBuildRun; ++e) h[e] = (uint32_t)n;
-      // token i of the hashes of the run: a window of tokens that moves back
-      int t[kBuildRun];
-#pragma unroll
-      for (int e = 0; e < kBuildRun; ++e) t[e] = M[min(j + e, L - 1)];
-      for (int i = 0; i < n; ++i) {
-        const int older = M[max(min(j, L - 1) - i - 1, 0)];
-#pragma unroll
-        for (int e = 0; e < kBuildRun; ++e) h[e] = ng_mix(h[e], (uint32_t)t[e]);
-#pragma unroll
-        for (int e = kBuildRun - 1; e > 0; --e) t[e] = t[e - 1];
-        t[0] = older;
-      }
       uint32_t mine = 0;
+      if (j <= L - 2) {   // the waves beyond the context skip the hashes
 #pragma unroll
-      for (int e = 0; e < kBuildRun; ++e)
-        if (j + e <= L - 2 && (int)((ng_finish(h[e]) & lv.mask) / kNgRegion) == region) mine |= 1u << e;
+        for (int e = 0; e < kBuildRun; ++e) h[e] = (uint32_t)n;
+        // token i of the hashes of the run: a window of tokens that moves back
+        int t[kBuildRun];
+#pragma unroll
+        for (int e = 0; e < kBuildRun; ++e) t[e] = M[min(j + e, L - 1)];
+        for (int i = 0; i < n; ++i) {
+          const int older = M[max(j - i - 1, 0)];
+#pragma unroll
+          for (int e = 0; e < kBuildRun; ++e) h[e] = ng_mix(h[e], (uint32_t)t[e]);
+#pragma unroll
+          for (int e = kBuildRun - 1; e > 0; --e) t[e] = t[e - 1];
+          t[0] = older;
+        }
+#pragma unroll
+        for (int e = 0; e < kBuildRun; ++e) {
+          h[e] = ng_finish(h[e]) & (uint32_t)lv.mask;
+          if (j + e <= L - 2 && (int)(h[e] / kNgRegion) == region) mine |= 1u << e;
+        }
+      }
       int found;
       int at = count + build_scan(__popc(mine), s.red, &found);
       count += found;
       const bool last = j0 + kBuildThreads * kBuildRun > L - 2;
       for (;;) {
         int k = at;
-        for (uint32_t m = mine; m; m &= m - 1, ++k)
-          if (k >= 0 && k < kBuildItems) s.pos[k] = j + __builtin_ctz(m);
+#pragma unroll
+        for (int e = 0; e < kBuildRun; ++e) {
+          if ((mine >> e & 1u) == 0u) continue;
+          if (k >= 0 && k < kBuildItems) {
+            s.pos[k] = j + e;
+            s.slot[k] = (uint16_t)(h[e] & rm);
+          }
+          ++k;
+        }
         if (count < kBuildItems && !last) break;
         __syncthreads();   // the list (and, the first time, the empty region) is written
         use(min(count, kBuildItems));
