@@ -719,13 +719,14 @@ __global__ __launch_bounds__(kBuildThreads) void ngram_build_kernel(const NgArgs
     });
 }
 
-// The headers of a build: nothing in use, the length it will reflect.
-__global__ void ngram_header_kernel(const NgArgs a) {
+// The headers of a build: nothing in use, the length it will reflect, and
+// whether the update kernel has the level to build (by the overflow mark).
+__global__ void ngram_header_kernel(const NgArgs a, int unbuilt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.B * a.n_max) return;
   const int b = i / a.n_max;
   const NgLevel lv = ng_level(a.index, b, i - b * a.n_max + 1, a.n_max, a.L_stride);
-  *lv.hdr = NgHeader{0, min(max(a.lens[b], 0), a.L_stride), 0, kNgMagic};
+  *lv.hdr = NgHeader{0, min(max(a.lens[b], 0), a.L_stride), unbuilt, kNgMagic};
 }
 
 // The lexical match of sequence b from its (up-to-date) index, by the first
@@ -874,19 +875,34 @@ __device__ void ng_match_seq(const NgArgs& a, int b, int32_t* __restrict__ cand_
 }  // namespace
 
 hipError_t launch_ngram_build(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max,
-                               void* index, hipStream_t stream) {
+                              void* index, hipStream_t stream) {
   const NgArgs a{tokens, lens, index, B, L_stride, n_max};
-  hipLaunchKernelGGL(ngram_header_kernel, dim3((B * n_max + 255) / 256), dim3(256), 0, stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const size_t slots = ngram_slots(L_stride);
   const unsigned regions = (unsigned)((slots + kNgRegion - 1) / kNgRegion);
-  hipLaunchKernelGGL(ngram_build_kernel, dim3(regions, n_max, B), dim3(kBuildThreads), 0, stream, a);
-  // One region holds every n-gram of its context.  Of several, one can get more
-  // than it has slots (chosen tokens; never seen in text); the update kernel
-  // then builds that level anew, going on in the next region, and finds
-  // nothing to do in the others.
-  if ((e = hipGetLastError()) != hipSuccess || regions == 1) return e;
+  // A region's workgroup hashes the whole row, one such workgroup fits a CU,
+  // and a row has a region per 2048 to 4096 tokens of capacity: its time, about
+  // (18 + levels) / 16 ns a position and round of 256 workgroups, grows with
+  // the square of the row.  The update kernel takes 65 ns a position, more
+  // beyond some 600 (sequence, level) pairs, whose workgroups share the CUs.
+  // Full rows, us by region / by level: 64 x 131072 tokens, 4 levels (32
+  // rounds) 6500 / 8540; 16 x 131072, 16 levels (32 rounds) 9080 / 8890; 2 x
+  // 131072, 64 levels (16 rounds) 10700 / 10300; 256 x 32768, 4 levels (32
+  // rounds, 1024 pairs) 2790 / 3560; 1 x 4194304, 4 levels (16 rounds) 70300 /
+  // 260000.
+  const long pairs = (long)B * n_max;
+  const long rounds = (regions * pairs + 255) / 256;
+  const bool by_region = rounds * (n_max + 18) <= 930 * std::max(pairs, 600L) / 600;
+  hipLaunchKernelGGL(ngram_header_kernel, dim3((B * n_max + 255) / 256), dim3(256), 0, stream, a, by_region ? 0 : 1);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (by_region) {
+    hipLaunchKernelGGL(ngram_build_kernel, dim3(regions, n_max, B), dim3(kBuildThreads), 0, stream, a);
+    // One region holds every n-gram of its context.  Of several, one can get
+    // more than it has slots (chosen tokens; never seen in text); the update
+    // kernel then builds that level anew, going on in the next region, and
+    // finds nothing to do in the others.
+    if ((e = hipGetLastError()) != hipSuccess || regions == 1) return e;
+  }
   hipLaunchKernelGGL(ngram_update_kernel, dim3(n_max, B), dim3(kNgThreads), 0, stream, a);
   return hipGetLastError();
 }

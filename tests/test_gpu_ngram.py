@@ -289,3 +289,24 @@ def test_index_one_workgroup_per_level(n_max):
         if not fused:
             idx.append(tok_d, lens_d)
         check(idx, tok, lens, tok_d, lens_d, n_max, f"step {step}", fused=fused)
+
+
+def test_index_build_by_level():
+    """A build whose rows have so many regions that the levels are built by the
+    kernel with one workgroup each (16 regions, 33 levels, 21 rounds of region
+    workgroups), over an older index, and an append on top."""
+    rng = np.random.default_rng(3)
+    B, L, n_max = 10, 50000, 33
+    cap = L + 40
+    tok = rng.integers(0, 30, (B, cap)).astype(np.int32)
+    tok[1] = rng.integers(0, 100000, cap)
+    tok[2] = 5
+    tok[3, L - 40:L] = tok[3, 777:817]
+    lens = np.array([L, L, 3000, L - 1, 70, 0, 257, 300, 2, 1], np.int32)
+    tok_d, lens_d = torch.from_numpy(tok).cuda(), torch.from_numpy(lens).cuda()
+    idx = adapld.NgramIndex(B, cap, n_max).build(tok_d, torch.from_numpy(lens // 2).cuda())
+    idx.build(tok_d, lens_d)
+    check(idx, tok, lens, tok_d, lens_d, n_max, "build")
+    lens += 30
+    lens_d.copy_(torch.from_numpy(lens))
+    check(idx, tok, lens, tok_d, lens_d, n_max, "append", fused=True)
