@@ -55,6 +55,19 @@ def test_lexical_word_edges(L, n_max):
     check(*contexts(L, n_max, 1000 * n_max + L), n_max)
 
 
+@pytest.mark.parametrize("L", [64, 130, 512, 1024, 4000, 8192])
+def test_lexical_members_per_word(L):
+    """Around the number of members per word from which the waves write their
+    words with a lane per member: tokens of period 7, 8 and 9, and words full
+    at one end of the context only."""
+    t = np.arange(L)
+    rows = [t % 7, t % 8, t % 9, np.where(t < L // 2, t + 10, 3), np.where(t < L // 8, 3, t + 10)]
+    rows[4][-1] = 3
+    lens = np.array([L, L, L - 1, L, L], np.int32)
+    for n_max in (1, 3):
+        check(np.stack(rows).astype(np.int32), lens, n_max)
+
+
 @pytest.mark.parametrize("n_max", [1, 5, 64])
 def test_lexical_several_pieces(n_max):
     """Two and three pieces: matches that end just after a piece boundary, and
