@@ -143,13 +143,16 @@ def _ptr(t, name, dtypes, shape=None, nullable=False):
     return t.data_ptr()
 
 
-# The current device's current stream as an integer, without a Stream object.
+# The current device's current stream as an integer, without a Stream object
+# (None in a torch build that lacks the call).
 _current_device = torch.cuda.current_device
-_raw_stream = torch._C._cuda_getCurrentRawStream
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
-    return _raw_stream(_current_device()) if stream is None else stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    return torch.cuda.current_stream().cuda_stream if _raw_stream is None else _raw_stream(_current_device())
 
 
 def workspace_bytes(op, B, L_stride, d=0, k=0, T_max=0, Hq=0, Hkv=0, D=0) -> int:

@@ -274,6 +274,27 @@ def test_step_workspace_is_one_partial_per_split(lib, B, L, d, k, T, Hq, Hkv):
     assert f(*args) in (INVALID, -5)
 
 
+def test_package_imports_without_the_raw_stream_call():
+    """torch's call for the current stream as an integer is a private name: a
+    build of torch without it still imports the package, and calls fall back to
+    the public one."""
+    import subprocess
+    import sys
+    code = """
+import torch
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    del torch._C._cuda_getCurrentRawStream
+from paper_2606_05742_amd import binding
+class Stream:
+    cuda_stream = 41
+torch.cuda.current_stream = Stream
+assert binding._stream(None) == 41
+Stream.cuda_stream = 42
+assert binding._stream(Stream()) == 42
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)
+
+
 def test_step_noalloc_validation(lib):
     """The allocation-free step refuses, before any HIP call, sizes whose
     workspace exceeds its device array (host-only checks: no GPU needed)."""
