@@ -31,9 +31,9 @@
 // of hash bits and index forms the groups; a batch holding two different
 // n-grams with equal bits falls back to one position at a time); a level that
 // was never built, or whose context shrank or pool overflowed, is rebuilt
-// from scratch by its wave.  With the match fused in, the first
-// wave then answers the lexical match from the levels just brought up to
-// date, so an iteration costs one launch.
+// from scratch by its wave.  With the match fused in, every wave looks the
+// last n tokens up in its own level beside its insertions, so an iteration
+// costs one launch.
 //
 // match kernel: one workgroup per sequence; lane n-1 of the first wave looks
 // up the last n tokens at level n, the longest level with a hit gives n*,
@@ -729,11 +729,6 @@ __global__ void ngram_header_kernel(const NgArgs a, int unbuilt) {
   *lv.hdr = NgHeader{0, min(max(a.lens[b], 0), a.L_stride), unbuilt, kNgMagic};
 }
 
-// The lexical match of sequence b from its (up-to-date) index, by the first
-// wave of the workgroup: lane n-1 looks up level n; writes the outputs.
-__device__ void ng_match_seq(const NgArgs& a, int b, int32_t* __restrict__ cand_pos, int32_t* __restrict__ cand_count,
-                             int32_t* __restrict__ match_n, int* s_n, int* s_off, int* s_cnt);
-
 // Appending, one wave per level (n_max <= kNgAppendWaves), each inserting its
 // level's new positions 64 at a time; with MATCH every wave also looks up the
 // last n tokens in its level, beside the last insertions, and the workgroup
@@ -815,13 +810,8 @@ __global__ __launch_bounds__(kNgAppendWaves * kWave) void ngram_append_kernel(co
   }
 }
 
-__global__ __launch_bounds__(kNgThreads) void ngram_match_kernel(const NgArgs a, int32_t* __restrict__ cand_pos,
-                                                                 int32_t* __restrict__ cand_count,
-                                                                 int32_t* __restrict__ match_n) {
-  __shared__ int s_n, s_off, s_cnt;
-  ng_match_seq(a, blockIdx.x, cand_pos, cand_count, match_n, &s_n, &s_off, &s_cnt);
-}
-
+// The lexical match of sequence b from its (up-to-date) index, by the first
+// wave of the workgroup: lane n-1 looks up level n; writes the outputs.
 __device__ void ng_match_seq(const NgArgs& a, int b, int32_t* __restrict__ cand_pos, int32_t* __restrict__ cand_count,
                              int32_t* __restrict__ match_n, int* s_n, int* s_off, int* s_cnt) {
   const int lane = lane_id();
@@ -872,6 +862,13 @@ __device__ void ng_match_seq(const NgArgs& a, int b, int32_t* __restrict__ cand_
   }
 }
 
+__global__ __launch_bounds__(kNgThreads) void ngram_match_kernel(const NgArgs a, int32_t* __restrict__ cand_pos,
+                                                                 int32_t* __restrict__ cand_count,
+                                                                 int32_t* __restrict__ match_n) {
+  __shared__ int s_n, s_off, s_cnt;
+  ng_match_seq(a, blockIdx.x, cand_pos, cand_count, match_n, &s_n, &s_off, &s_cnt);
+}
+
 }  // namespace
 
 hipError_t launch_ngram_build(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max,
@@ -910,7 +907,7 @@ hipError_t launch_ngram_build(const int32_t* tokens, const int32_t* lens, int B,
 hipError_t launch_ngram_append(const int32_t* tokens, const int32_t* lens, int B, int L_stride, int n_max, void* index,
                                int32_t* cand_pos, int32_t* cand_count, int32_t* match_n, hipStream_t stream) {
   const NgArgs a{tokens, lens, index, B, L_stride, n_max};
-  if (n_max > kNgAppendWaves) {   // more levels than one workgroup's waves: the build kernel's path
+  if (n_max > kNgAppendWaves) {   // more levels than one workgroup's waves: one workgroup for each
     hipLaunchKernelGGL(ngram_update_kernel, dim3(n_max, B), dim3(kNgThreads), 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !cand_pos) return e;
