@@ -138,8 +138,7 @@ __device__ __forceinline__ void dma16_s(const void* gbase, uint32_t voff, uint32
 }
 // The same with the non-temporal hint, for tiles that no other workgroup
 // reads (one row group): the caches then treat them as streaming.  With two or
-// more row groups the tiles
-// must stay in L2 for the other readers.
+// more row groups the tiles must stay in L2 for the other readers.
 __device__ __forceinline__ void dma16_s_stream(const void* gbase, uint32_t voff, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                :
@@ -196,8 +195,10 @@ __device__ __forceinline__ void wait_tile_and_sync(int later) {
 // the second reader of a K/V tile finds it in that XCD's L2.
 constexpr int kPlanSeqs = kWave;       // most sequences ordered together: one per lane
 constexpr int kPlanRowgroups = 0x7fff; // most row groups of one sequence in an order
-constexpr int kCostWide = 16;          // cost of one tile of a row group of 5 to 8 blocks: two waves' rows per SIMD
-constexpr int kCostNarrow = 12;        // of one of up to 4 blocks
+// Cost of one tile of a row group of 5 to 8 blocks (two waves' rows per SIMD)
+// and of up to 4, for the order alone: what a workgroup takes beside others of
+// its round.  The plan weighs the two shapes with constants of its own.
+constexpr int kCostWide = 16, kCostNarrow = 12;
 constexpr int kCUs = 256;
 
 // x / d for 0 <= x, 0 < d by a reciprocal and one correction (the compiler's
@@ -873,7 +874,8 @@ VerifyPlan plan_verify(int B, int L_stride, int T_max, int Hq, int Hkv) {
   // the LDS ring takes 128 KiB) times one workgroup's time, which is its
   // per-SIMD share of row x key work plus a fixed start-up cost, plus the
   // combine kernel when the context is split.  The constants are in units of
-  // one SIMD's time for 32 rows x 64 keys with two waves per SIMD.
+  // one SIMD's time for 32 rows x 64 keys with two waves per SIMD.  The plan
+  // decides where contexts are cut, and with that the results' bits.
   constexpr double kStartTiles = 12.0;    // start-up and drain of one workgroup
   constexpr double kCombineTiles = 6.0;   // the combine launch and its traffic
   // With more than one row group, every tile goes to LDS once per row group
