@@ -30,9 +30,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 # figures hold only for the kernel sources they were taken on.
 VERIFY_TRAFFIC = {
     "workload": "b16_l8192_gqa32x8",
-    "source_sha256": "13fc8e91a51acb342bf8b43b9b8b6f195593dd092a1d7c0ef93bfb64c0522f4c",
-    "fetch_kib": 273533.6,
-    "write_kib": 16567.6,
+    "source_sha256": "fa08570e4b33c74bec8d4799b7e4a1ecaafa57096a047a8b17471d906525fbae",
+    "fetch_kib": 276116.8,
+    "write_kib": 16567.9,
     "fetch_scale": 2.0,
     "write_scale": 1.0,
 }
