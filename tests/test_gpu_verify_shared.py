@@ -1,8 +1,8 @@
 """GPU parity of adapld_tree_verify_attn where a batch takes several rounds of
 workgroups, which are shared out by context length and tree size, and at sizes
 beside those: lengths from empty to the capacity, trees from none to T_max, batches at and
-around the 64 sequences that are planned together, and head counts that are
-and are not multiples of the eight XCDs."""
+around the 64 sequences that one plan orders, and head counts that are and are
+not multiples of the eight XCDs."""
 import numpy as np
 import pytest
 import torch
@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,L,T,HQ,HKV", [
-    (17, 4200, 20, 16, 8),     # pairs of waves, split, more than 16 sequences
-    (5, 9001, 60, 28, 4),      # whole-workgroup blocks, split, units over two XCD groups
-    (3, 20000, 12, 12, 12),    # 12 heads: four XCD columns, three heads each
-    (65, 300, 40, 40, 8),      # unsplit, two plans, the second of one sequence
+    (17, 4200, 20, 16, 8),     # pairs of waves, more than 16 sequences
+    (5, 9001, 60, 28, 4),      # whole-workgroup blocks, split, a kv head for every other XCD
+    (3, 20000, 12, 12, 12),    # 12 kv heads, split
+    (65, 300, 40, 40, 8),      # unsplit, two plans of 33 and 32 sequences
     (64, 200, 70, 16, 5),      # an odd head count, 64 sequences
     (130, 200, 70, 8, 2),      # two row groups, three plans
     (66, 130, 137, 16, 2),     # five row groups
