@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
     (64, 200, 70, 16, 5),      # an odd head count, 64 sequences
     (130, 200, 70, 8, 2),      # two row groups, three plans
     (66, 130, 137, 16, 2),     # five row groups
-    (70, 400, 30, 32, 2),      # pairs of waves, four row groups
+    (70, 400, 30, 32, 2),      # whole-workgroup blocks, two row groups
 ])
 def test_shared_batches(B, L, T, HQ, HKV):
     HQ = HQ // HKV * HKV
